@@ -326,7 +326,8 @@ int les_get_ghosted(les_handle* h, float* u, float* v, float* w);
  * family, the summed event-bracketed device time and the number of timed
  * launches.  Families: 0 nu_t, 1 tendency, 2 inflow, 3 rhs, 4 SOR sweep
  * launch (a half-sweep, a whole iteration with the fused variants 8-11,
- * two with 12-13), 5 residual check (sampled like the sweeps: the launches
+ * two with 12-13; solves by the resident kernel: its whole time, checks and
+ * folds included, and every iteration counted as a launch), 5 residual check (sampled like the sweeps: the launches
  * count is that of the sampled intervals), 6 rebase, 7 projection, 8
  * boundary refresh.  reset = 1 clears the counters after reading. */
 #define LES_NUM_KERNELS 9
@@ -355,6 +356,16 @@ int les_get_timing(les_handle* h, les_timing* out, int32_t reset);
  * blocks per compute unit; they need check_every to be a multiple of 4 and
  * are not used by ensembles.  Every variant computes the same per-cell
  * arithmetic, so results are bitwise independent of the choice.
+ *
+ * Uniform grids whose pressure system fits the chip's registers and LDS (up
+ * to about 10 million cells) are solved by a resident kernel instead, one
+ * cooperative launch for thousands of iterations, with the same arithmetic
+ * and the same results bit for bit; sweep launches serve the other grids,
+ * ensembles and the allocation-free solve.  les_set_sor_variant turns it off
+ * for the handle (its solves then use the variant asked for), les_autotune
+ * turns it on where it is faster than every variant.  Its face buffers (tens
+ * of MB at most) are allocated at the handle's first solve; without the
+ * memory for them the handle uses its sweep variant.
  *
  * Autotuner: times every variant for reps back-to-back pairs of launches
  * on this handle's grid, keeps the fastest for all later solves of the

@@ -17,7 +17,8 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libles.so")
 SOURCES = ["kernels_step.hip", "kernels_sor.hip", "ensemble.hip", "les_api.hip", "lesnet.hip",
-           "warm.hip", "twinned.hip", "noalloc.hip", "netdata.hip"]
+           "warm.hip", "twinned.hip", "noalloc.hip", "netdata.hip",
+           "resident.hip"]
 
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",

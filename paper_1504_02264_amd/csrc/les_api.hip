@@ -277,6 +277,96 @@ SolveGraph* solve_graph(les_handle* h, const PBufs& P, int var, int K, int R, do
     return best;
 }
 
+// ------------------------------------------------------- resident solver
+// Iterations of one resident launch: the GPU goes back to other work between
+// launches, and a launch's fixed cost (about 20 us) is lost in them.  A check
+// interval runs within one launch, so the longest intervals keep to the sweeps.
+constexpr int kResidentIters = 8192, kResidentMaxK = 32768;
+
+bool resident_runs(const les_handle* h) { return h->resident && h->prm.check_every <= kResidentMaxK; }
+
+// Face buffers of the resident solver; without the memory for them the handle
+// goes on with sweep launches.
+bool resident_ready(les_handle* h) {
+    if (h->res_mem) return true;
+    const size_t bytes = resident_bytes(h->rplan);
+    if (hipMalloc(&h->res_mem, bytes) == hipSuccess &&
+        launch_fill(h->stream, (float*)h->res_mem, (long long)(bytes / 4), 0.f) == hipSuccess)
+        return true;
+    (void)hipGetLastError();
+    if (h->res_mem) (void)hipFree(h->res_mem);
+    h->res_mem = nullptr;
+    h->resident = false;
+    return false;
+}
+
+// Tags of one launch (used once: when they run out the buffers are cleared).
+hipError_t resident_take_tags(les_handle* h, int iters, int K, unsigned& tag) {
+    const unsigned need = resident_tags(iters, K);
+    if (h->res_tag > 0xffffffffu - need) {
+        const hipError_t e = launch_fill(h->stream, (float*)h->res_mem, (long long)(resident_bytes(h->rplan) / 4), 0.f);
+        if (e != hipSuccess) return e;
+        h->res_tag = 1;
+    }
+    tag = h->res_tag;
+    h->res_tag += need;
+    return hipSuccess;
+}
+
+enum { RES_RAN, RES_REFUSED, RES_LOST };
+
+// The solve after its set-up rebase, by resident launches (resident.hip).
+// how: RES_REFUSED if none could be launched (nothing has changed then);
+// RES_LOST if a block waited in vain, as when another process holds part of
+// the chip: ph + pd is then an iterate, taken cell by cell at the moment its
+// block gave up, and the sweeps go on from it.
+int run_resident(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve_stats* out, int& how) {
+    const Geo& g = h->g;
+    hipStream_t st = h->stream;
+    Ctl* ctl = h->f.ctl;
+    const int K = h->prm.check_every, R = h->prm.rebase_every;
+    how = RES_REFUSED;
+    const int iters = std::min(max_iter, std::max(kResidentIters / K, 1) * K);
+    Ctl& hc = *h->h_ctl;
+    do {
+        unsigned tag = 0;
+        CK(resident_take_tags(h, iters, K, tag));
+        if (max_iter > 0) {
+            const hipError_t e = timed(
+                h, KN_SOR, kNoTag,
+                [&] { return launch_resident(g, st, h->rplan, P, ctl, h->res_mem, h->prm.omega, K, R, iters, tag); }, 0);
+            if (e != hipSuccess && how == RES_REFUSED) {
+                (void)hipGetLastError();
+                h->resident = false;
+                return LES_OK;
+            }
+            CK(e);
+        }
+        how = RES_RAN;
+        CK(hipMemcpyAsync(&hc, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+        CK(hipStreamSynchronize(st));
+        if (hc.pad_u[0]) {
+            how = RES_LOST;
+            h->resident = false;
+            return LES_OK;
+        }
+    } while (!hc.done && max_iter > 0);
+    if (h->prm.timing) {   // every iteration is timed, none sampled
+        tresolve(h, kNoTag);
+        h->tcount[KN_SOR] += hc.m;
+    }
+    if (out) {
+        out->iters = hc.m;
+        out->resid = hc.resid;
+        out->rhs_norm = std::sqrt(hc.rhs2);
+        out->reltmp2 = hc.reltmp2;
+        out->converged = (hc.done == 1 || (hc.done == 0 && hc.resid <= tol)) ? 1 : 0;
+    }
+    if (hc.done == 3 || !std::isfinite(hc.rhs2)) return set_err(h, LES_ENONFINITE, "non-finite residual norm");
+    if (hc.done == 2 || (hc.done == 0 && !(hc.resid <= tol))) return LES_NOT_CONVERGED;
+    return LES_OK;
+}
+
 // ------------------------------------------------------------- SOR driver
 // Preconditions: ctl initialised, P.rhs filled, ctl->rhs2 computed.
 // Runs the set-up rebase, then check intervals of K iterations (two
@@ -389,10 +479,21 @@ int run_solve(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve
         return LES_OK;
     };
 
+    long long c = 0;
     CK(launch_fold(g, st, P, ctl));
     CK(tm(KN_REBASE, 0, [&] { return launch_rebase(g, st, P, part, nullptr, nullptr, 0, ctl, 0); }));
+    if (!direct && resident_runs(h) && resident_ready(h)) {
+        int how = RES_RAN;
+        const int rc = run_resident(h, P, tol, max_iter, out, how);
+        if (how == RES_RAN || rc != LES_OK) return rc;
+        if (how == RES_LOST) {
+            c = (h->h_ctl->m + K - 1) / K;
+            CK(hipMemsetAsync(&ctl->done, 0, sizeof(int), st));
+            CK(launch_fold(g, st, P, ctl));
+            CK(launch_rebase(g, st, P, part, nullptr, nullptr, 0, ctl, 0));
+        }
+    }
     const long long n_checks = max_iter > 0 ? ((long long)max_iter + K - 1) / K : 0;
-    long long c = 0;
     // batches of 2, 2, 4 intervals (a solve that converges at once is
     // noticed early), then 8, 16, 32, 64 (capped below): from interval 8 on
     // every batch starts on a multiple of kSolveGraphChecks
@@ -704,6 +805,12 @@ int create_impl(const les_grid* gr, const les_spacing* s, const double* const* w
     h->prof.assign((size_t)g.nz, 0.f);
     h->prof1.assign((size_t)g.nz, 0.f);
     h->sor_variant = sor_default_variant(g);
+    int coop = 0, cus = 0;
+    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, h->device) == hipSuccess && coop &&
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess) {
+        h->rplan = resident_plan(g, cus);
+        h->resident = h->rplan.shape >= 0;
+    }
     *out = h;
     return LES_OK;
 }
@@ -746,6 +853,7 @@ void les_destroy(les_handle* h) {
     if (h->stream) (void)hipStreamSynchronize(h->stream);
     if (h->arena) (void)hipFree(h->arena);
     if (h->solve_arena) (void)hipFree(h->solve_arena);
+    if (h->res_mem) (void)hipFree(h->res_mem);
     warm_free(h);
     twinned_free(h);
     if (h->h_ctl) (void)hipHostFree(h->h_ctl);
@@ -1200,6 +1308,27 @@ int les_autotune(les_handle* h, int32_t reps, int32_t* chosen, double* us_per_sw
             best_v = v;
         }
     }
+    // the resident solver on the same zero system: one interval of reps
+    // iterations and its check per launch (it stops there, the norm being 0)
+    h->resident = h->rplan.shape >= 0;
+    if (resident_runs(h) && resident_ready(h)) {
+        const int n = std::max(8 * reps, 128);
+        float ms = 0.f;
+        for (int r = 0; r < 2 && h->resident; ++r) {   // the first launch loads the code
+            unsigned tag = 0;
+            CK(launch_ctl_init(s, h->f.ctl, 1e-30, 1 << 30, n));
+            CK(resident_take_tags(h, n, n, tag));
+            CK(hipEventRecord(a, s));
+            if (launch_resident(g, s, h->rplan, h->S, h->f.ctl, h->res_mem, 1.0, n, 1 << 30, n, tag) != hipSuccess) {
+                (void)hipGetLastError();
+                h->resident = false;
+            }
+            CK(hipEventRecord(b, s));
+            CK(hipEventSynchronize(b));
+            CK(hipEventElapsedTime(&ms, a, b));
+        }
+        if (1e3 * ms / (2.0 * n) >= best) h->resident = false;
+    }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     for (int c = 0; c < 2; ++c) CK(launch_fill(s, h->S.pd[c], g.ctot, 0.f));
@@ -1217,6 +1346,7 @@ int les_set_sor_variant(les_handle* h, int32_t variant) {
     if (sor_fused2(variant) && (h->prm.check_every & 3))
         return set_err(h, LES_EINVAL, "two-iteration sweep variants need a check interval that is a multiple of 4");
     h->sor_variant = variant;
+    h->resident = false;
     return LES_OK;
 }
 

@@ -195,6 +195,15 @@ struct SolveGraph {
     hipGraphExec_t exec[3] = {nullptr, nullptr, nullptr};
     uint64_t used = 0;
 };
+// Decomposition of a grid for the resident solver (resident.hip): shape -1 if
+// the grid does not fit the chip's registers.
+struct ResPlan {
+    int shape;
+    int nbx, nby, nbz;   // tiles per axis
+    int w, g;            // half-cells per row of a tile, ghost columns on each side of it
+    unsigned blocks;
+    long long words, xwords;   // face and ghost words per block and publication
+};
 }  // namespace les
 
 struct les_handle {
@@ -236,6 +245,11 @@ struct les_handle {
     hipEvent_t ev[2] = {nullptr, nullptr};
     les::SolveGraph sgraph[3];   // run_solve's graph cache (timing off)
     uint64_t sgraph_tick = 0;
+    // resident solver: whether solves take it, its plan, face buffers and next tag
+    bool resident = false;
+    les::ResPlan rplan{};
+    void* res_mem = nullptr;
+    uint32_t res_tag = 1;
     // twinned double-buffer comparison solver (twinned.hip): pairs, partials
     void* tw_q = nullptr;
     double* tw_part = nullptr;
@@ -367,6 +381,13 @@ hipError_t launch_sor_rb(const Geo& g, hipStream_t st, const PBufs& P, int parit
 // buffers as launch_sor_rb
 hipError_t launch_sor_rb2(const Geo& g, hipStream_t st, const PBufs& P, int parity, float omega,
                           int local_iter, double* rel0, double* rel1, const Ctl* ctl, int variant);
+// resident solver (resident.hip): up to `iters` more iterations of the solve
+// ctl describes (stopping tests included), the face buffers in mem
+ResPlan resident_plan(const Geo& g, int cus);
+size_t resident_bytes(const ResPlan& p);
+unsigned resident_tags(int iters, int K);
+hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const PBufs& P, Ctl* ctl, void* mem,
+                           double omega, int K, int R, int iters, unsigned tag);
 hipError_t launch_project(const Geo& g, hipStream_t st, float* us, float* vs, float* ws,
                           const PBufs& P);
 hipError_t launch_bc(const Geo& g, hipStream_t st, float* u, float* v, float* w);

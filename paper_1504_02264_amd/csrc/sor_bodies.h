@@ -1299,6 +1299,14 @@ __device__ __forceinline__ double diag64(const Geo& g, int i0, int j0, int k0) {
         return dx + dy + dz;
     }
 }
+// (A x) of a uniform-grid cell with value x and diagonal d; the order of the
+// products is pinned, so that every kernel rounds alike.
+__device__ __forceinline__ double op64(const Geo& g, float west, float east, float south, float north, float below,
+                                       float above, double d, float x) {
+    const double nb = fma(g.czd, (double)below + (double)above,
+                          fma(g.cxd, (double)west + (double)east, g.cyd * ((double)south + (double)north)));
+    return fma(-d, (double)x, nb);
+}
 template <bool STR = false>
 __device__ __forceinline__ double apply_A64(const Geo& g, const float* xo, const float* xn,
                                             long long e, int s, double d, int i0 = 0, int j0 = 0,
@@ -1312,10 +1320,7 @@ __device__ __forceinline__ double apply_A64(const Geo& g, const float* xo, const
                           wrow(g.wz, g.nz, 1, k0 + 1) * (double)xn[e + g.SP];
         return nb - d * (double)xo[e];
     } else {
-        const double nb = g.cxd * ((double)xn[e - 1 + s] + (double)xn[e + s]) +
-                          g.cyd * ((double)xn[e - g.S] + (double)xn[e + g.S]) +
-                          g.czd * ((double)xn[e - g.SP] + (double)xn[e + g.SP]);
-        return nb - d * (double)xo[e];
+        return op64(g, xn[e - 1 + s], xn[e + s], xn[e - g.S], xn[e + g.S], xn[e - g.SP], xn[e + g.SP], d, xo[e]);
     }
 }
 
