@@ -10,7 +10,7 @@
 // the launches (3 us each) and, from some million cells, by the 24 bytes per
 // cell and half-sweep that they move.  Per iteration against the best sweep
 // launches, MI355X: 64x64x32 with a check every 64: 2.8 us (was 7.5);
-// 150x150x90, a check every 4: 12.6 us (16.7); 300x300x90, a check every 64:
+// 150x150x90, a check every 4: 11.5 us (16.7); 300x300x90, a check every 64:
 // 11.5 us (16.5).
 //
 // Same per-cell arithmetic as the sweep launches (sor_nb / sor_relax, the
@@ -114,7 +114,18 @@ __device__ __forceinline__ int opaque_lane(int v) {
 __device__ __forceinline__ void put(u64* p, unsigned tag, float v) {
     __hip_atomic_store(p, ((u64)tag << 32) | __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-template <int RY, int RZ, int GY>
+// Element of a row of a colour array: the row's address is uniform, the
+// lane adds its half-index.
+__device__ __forceinline__ float* at(float* row, unsigned i) {
+    return (float*)((char*)row + 4u * i);
+}
+__device__ __forceinline__ float peek(const float* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void poke(float* p, float v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+    template <int RY, int RZ, int GY>
 struct Resident {
     typedef ResSmem<RY, RZ, GY> Smem;
     static_assert(RY % 2 == 0 && RZ % 2 == 0, "patch origins have even j + k, so a pair's phase is its colour");
@@ -201,10 +212,10 @@ struct Resident {
 #pragma unroll
             for (int z = 0; z < RZ; ++z) {
                 const bool ok = ((yk >> r) & (zk >> z) & 1) != 0;
-                const long long e = g.col(i, j + r, k + z);
+                const long long e = g.col(0, j + r, k + z);
                 float* pe = ((r + z) & 1) ? q1 : q0;
                 float* po = ((r + z) & 1) ? q0 : q1;
-                f(r, z, pe + e, in && ok, po + e, in_o && ok);
+                f(r, z, at(pe + e, (unsigned)i), in && ok, at(po + e, (unsigned)i), in_o && ok);
             }
     }
     template <bool COHERENT = false>
@@ -214,10 +225,19 @@ struct Resident {
             O[r][z] = oko ? (COHERENT ? peek(po) : *po) : 0.f;
         });
     }
-    __device__ __forceinline__ void store(float* const q[2], const Patch& E, const Patch& O) const {
+    // (the tile's own cells are in the registers)
+    __device__ __forceinline__ void load_ghosts(float* const q[2], Patch& E, Patch& O) const {
+        if (live && !own)
+            each(true, q[0], q[1], [&](int r, int z, const float* pe, bool oke, const float* po, bool oko) {
+                if (oke) E[r][z] = peek(pe);
+                if (oko) O[r][z] = peek(po);
+            });
+    }
+    template <bool COHERENT = false>
+    __device__ __forceinline__ void store(float* const (&q)[2], const Patch& E, const Patch& O) const {
         each(own, q[0], q[1], [&](int r, int z, float* pe, bool oke, float* po, bool oko) {
-            if (oke) *pe = E[r][z];
-            if (oko) *po = O[r][z];
+            if (oke) COHERENT ? poke(pe, E[r][z]) : (void)(*pe = E[r][z]);
+            if (oko) COHERENT ? poke(po, O[r][z]) : (void)(*po = O[r][z]);
         });
     }
 
@@ -303,7 +323,7 @@ struct Resident {
         for (int spin = 0;; ++spin) {   // a neighbour may be one refresh ahead
             bool ok = true;
             if (see) ok = (int)(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - n) >= 0;
-            if (dead || __all(ok)) break;
+            if (__builtin_expect(dead || __all(ok), 1)) break;
             if (spin >= kResSpin) dead = true;
         }
         asm volatile("" ::: "memory");   // no column before its flag
@@ -348,7 +368,7 @@ struct Resident {
 #pragma unroll
                         for (int r = 0; r < RY; ++r) ok = ok && (unsigned)(vz[r] >> 32) == tag;
                 }
-                if (dead || __all(ok)) break;
+                if (__builtin_expect(dead || __all(ok), 1)) break;
                 if (spin >= kResSpin) dead = true;
             }
         }
@@ -474,97 +494,140 @@ struct Resident {
     // (and the folded ph) there with agent-coherent stores, meet, and read
     // their cells' surroundings back with agent-coherent loads, so that the
     // sweeps keep the registers.
-    static __device__ __forceinline__ float peek(const float* p) {
-        return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    static __device__ __forceinline__ void poke(float* p, float v) {
-        __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
     // pd to memory; with FOLD, ph <- fl(ph + pd) and pd <- the exact rest
-    // (TwoSum) on the way.
+    // (TwoSum) on the way, a row of the patch per trip: 30 us at 300x300x90, 12
+    // bytes per cell (all of ph at once did not fit the registers: 46 us).
     template <bool FOLD>
-    __device__ __forceinline__ void leave(const Patch& E, const Patch& O) const {
-        auto cell = [&](float* pd, float* ph, float b) {
-            if constexpr (FOLD) {
-                const float x = peek(ph), f = x + b, bb = f - x;
-                poke(ph, f);
-                b = (x - (f - bb)) + (b - bb);
+    __device__ __forceinline__ void leave(Patch& E, Patch& O) const {
+        const Geo& g = a.g;
+        const int i = opaque_lane(ii), j = opaque(j0), k = opaque(k0), yk = opaque(yok), zk = opaque(zok);
+        const bool odd_last = 2 * i + 1 >= g.nx;   // an odd row has no last O cell
+        if (own) {
+#pragma unroll
+            for (int r = 0; r < RY; ++r) {
+                const long long e = g.col(0, j + r, k);
+                float be[RZ], bo[RZ], xe[RZ], xo[RZ];
+                if constexpr (FOLD)
+#pragma unroll
+                    for (int z = 0; z < RZ; ++z) {   // (outside the grid: its first cell's, unused)
+                        const long long ez = ((yk >> r) & (zk >> z) & 1) ? e + z * g.SP : g.col(0, 0, 0);
+                        xe[z] = *at(a.P.ph[(r + z) & 1] + ez, (unsigned)i);
+                        xo[z] = *at(a.P.ph[1 - ((r + z) & 1)] + ez, (unsigned)i);
+                    }
+#pragma unroll
+                for (int z = 0; z < RZ; ++z) {
+                    be[z] = E[r][z];
+                    bo[z] = O[r][z];
+                    if constexpr (FOLD) {
+                        two_sum(xe[z], be[z]);
+                        two_sum(xo[z], bo[z]);
+                        E[r][z] = be[z];
+                        O[r][z] = bo[z];
+                    }
+                }
+#pragma unroll
+                for (int z = 0; z < RZ; ++z) {
+                    if (!((yk >> r) & (zk >> z) & 1)) continue;
+                    const long long ez = e + z * g.SP;
+                    const int c = (r + z) & 1;
+                    poke(at(a.P.pd[c] + ez, (unsigned)i), be[z]);
+                    if constexpr (FOLD) poke(at(a.P.ph[c] + ez, (unsigned)i), xe[z]);
+                    if (odd_last) continue;
+                    poke(at(a.P.pd[1 - c] + ez, (unsigned)i), bo[z]);
+                    if constexpr (FOLD) poke(at(a.P.ph[1 - c] + ez, (unsigned)i), xo[z]);
+                }
+                asm volatile("" ::: "memory");   // a row at a time: the registers hold the tile
             }
-            poke(pd, b);
-        };
-        const long long off = a.P.ph[0] - a.P.pd[0], off1 = a.P.ph[1] - a.P.pd[1];   // both colours of a field lie alike
-        each(own, a.P.pd[0], a.P.pd[1], [&](int r, int z, float* pe, bool oke, float* po, bool oko) {
-            const bool odd = ((r + z) & 1) != 0;   // E's colour
-            if (oke) cell(pe, pe + pick(odd, off1, off), E[r][z]);
-            if (oko) cell(po, po + pick(odd, off, off1), O[r][z]);
-        });
+        }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // at the point of coherence before the blocks meet
     }
+    // x <- fl(x + b), b <- the exact rest
+    static __device__ __forceinline__ void two_sum(float& x, float& b) {
+        const float f = x + b, bb = f - x;
+        b = (x - (f - bb)) + (b - bb);
+        x = f;
+    }
     // Sum of squares over the tile of r = b - A x (float64), b = r0, x = pd; or,
-    // with REBASE, of rhs - A (ph + pd), storing r0 = rhs - A ph.  Rows are
-    // marched up in z: the planes of a column stay in registers.
+    // with REBASE, of rhs - A (ph + pd), storing r0 = rhs - A ph.  Two planes of
+    // a row at a time: their loads travel together, and few enough registers are
+    // taken to leave the sweeps theirs (whole rows, and marches that read each
+    // value once, made the compiler spill the tile in the sweeps: 12 -> 16 us per
+    // iteration at 300x300x90).  It is bound by its loads, about 40 bytes per cell
+    // that pass the caches by: 50 us at 300x300x90, 15 us at 150x150x90, of a fold
+    // and rebase of 130 and 45 us (156 and 60 with one plane at a time).
     template <bool REBASE>
     __device__ __forceinline__ double residual() const {
+        constexpr int kSlab = 2;
         const Geo& g = a.g;
         double s = 0.0;
         const int i = opaque_lane(ii), jb = opaque(j0), kb = opaque(k0);
-        const bool in = live;
-        if (kb >= g.nz) return 0.0;
-#pragma unroll 1
-        for (int r = 0; r < RY; ++r) {
-            const int j = jb + r;
-            if (j >= g.ny) break;
-            struct Pair {
-                float e, o;
-            };
-            // the pair of a field at plane k, row j + dj (zeros outside the grid's arrays)
-            auto pair = [&](float* const q[2], int dj, int k) -> Pair {
-                const bool odd = ((j + dj + k) & 1) != 0;
-                const float* q0 = q[0];
-                const float* q1 = q[1];
-                const long long e = g.col(in ? i : 0, j + dj, k);
-                Pair v;
-                v.e = peek(pick(odd, q1, q0) + e);
-                v.o = peek(pick(odd, q0, q1) + e);
-                v.e = in ? v.e : 0.f;
-                v.o = in ? v.o : 0.f;
-                return v;
-            };
-            Pair db = pair(a.P.pd, 0, kb - 1), dc = pair(a.P.pd, 0, kb), hb{}, hc{};
-            if constexpr (REBASE) {
-                hb = pair(a.P.ph, 0, kb - 1);
-                hc = pair(a.P.ph, 0, kb);
-            }
-#pragma unroll 3
-            for (int z = 0; z < RZ; ++z) {
-                const int k = kb + z;
-                if (k >= g.nz) break;
-                const Pair dt = pair(a.P.pd, 0, k + 1), ds = pair(a.P.pd, -1, k), dn = pair(a.P.pd, 1, k);
-                const bool odd = ((j + k) & 1) != 0;
-                const long long e = g.col(in ? i : 0, j, k);
-                const double de = diag64(g, 2 * i, j, k), dd = diag64(g, 2 * i + 1, j, k);
-                const double ae = op64(g, dc.o, from_left(dc.o), ds.e, dn.e, db.e, dt.e, de, dc.e);
-                const double ao = op64(g, dc.e, from_right(dc.e), ds.o, dn.o, db.o, dt.o, dd, dc.o);
-                double be, bo;
-                if constexpr (REBASE) {
-                    const Pair ht = pair(a.P.ph, 0, k + 1), hs = pair(a.P.ph, -1, k), hn = pair(a.P.ph, 1, k);
-                    const float* re = pick(odd, a.P.rhs[1], a.P.rhs[0]) + e;
-                    const float* ro = pick(odd, a.P.rhs[0], a.P.rhs[1]) + e;
-                    be = (double)*re - op64(g, hc.o, from_left(hc.o), hs.e, hn.e, hb.e, ht.e, de, hc.e);
-                    bo = (double)*ro - op64(g, hc.e, from_right(hc.e), hs.o, hn.o, hb.o, ht.o, dd, hc.o);
-                    if (own) poke(pick(odd, a.P.r0[1], a.P.r0[0]) + e, (float)be);
-                    if (own_o) poke(pick(odd, a.P.r0[0], a.P.r0[1]) + e, (float)bo);
-                    hb = hc;
-                    hc = ht;
-                } else {
-                    be = (double)peek(pick(odd, a.P.r0[1], a.P.r0[0]) + e);
-                    bo = (double)peek(pick(odd, a.P.r0[0], a.P.r0[1]) + e);
+        const unsigned il = live ? (unsigned)i : 0u;
+        struct Column {
+            float e[kSlab + 2], o[kSlab + 2];   // planes k - 1 .. k + kSlab
+        };
+        // kSlab planes of row j from k (and those around them) of a field; past the
+        // grid's outer row or plane: those again, not used
+        auto column = [&](float* const (&q)[2], int j, int k, bool around, Column& x) {
+            j = min(j, g.ny);
+            const bool odd = ((j + k) & 1) != 0;
+            float* q0 = pick(odd, q[0], q[1]) + g.col(0, j, k - 1);   // E's at the first plane
+            float* q1 = pick(odd, q[1], q[0]) + g.col(0, j, k - 1);
+#pragma unroll
+            for (int p = 0; p < kSlab + 2; ++p) {
+                if (around || (p != 0 && p != kSlab + 1)) {
+                    x.e[p] = peek(at((p & 1) ? q1 : q0, il));
+                    x.o[p] = peek(at((p & 1) ? q0 : q1, il));
                 }
-                const double te = be - ae, to = bo - ao;
-                if (own) s += te * te;
-                if (own_o) s += to * to;
-                db = dc;
-                dc = dt;
+                const long long up = k + p <= g.nz ? g.SP : 0;
+                q0 += up;
+                q1 += up;
+            }
+        };
+        auto mask = [&](Column& x) {   // lanes without a cell: 0
+#pragma unroll
+            for (int p = 0; p < kSlab + 2; ++p) {
+                x.e[p] = live ? x.e[p] : 0.f;
+                x.o[p] = live ? x.o[p] : 0.f;
+            }
+        };
+        float* const base[2] = {REBASE ? a.P.rhs[0] : a.P.r0[0], REBASE ? a.P.rhs[1] : a.P.r0[1]};
+        const double dxe = (2 * i > 0 ? g.cxd : 0.0) + (2 * i < g.nx - 1 ? g.cxd : (g.outflow ? 2.0 * g.cxd : 0.0));
+        const double dxo = g.cxd + (2 * i + 1 < g.nx - 1 ? g.cxd : (g.outflow ? 2.0 * g.cxd : 0.0));
+#pragma unroll 1
+        for (int q = 0; q < NP / kSlab; ++q) {
+            const int j = jb + q / (RZ / kSlab), kz = kb + q % (RZ / kSlab) * kSlab;
+            if (j >= g.ny || kz >= g.nz) continue;
+            Column dc, ds, dn, hc, hs, hn, bc;
+            column(a.P.pd, j, kz, true, dc);
+            column(a.P.pd, j - 1, kz, false, ds);
+            column(a.P.pd, j + 1, kz, false, dn);
+            if constexpr (REBASE) {
+                column(a.P.ph, j, kz, true, hc);
+                column(a.P.ph, j - 1, kz, false, hs);
+                column(a.P.ph, j + 1, kz, false, hn);
+            }
+            column(base, j, kz, false, bc);
+            mask(dc);
+            if constexpr (REBASE) mask(hc);
+            const double dy = (j > 0 ? g.cyd : 0.0) + (j < g.ny - 1 ? g.cyd : 0.0);
+#pragma unroll
+            for (int z = 0; z < kSlab; ++z) {
+                const int k = kz + z, p = z + 1;
+                const bool ok = k < g.nz, odd = ((j + k) & 1) != 0;
+                const double dz = (k > 0 ? g.czd : 0.0) + (k < g.nz - 1 ? g.czd : 0.0);
+                const double de = dxe + dy + dz, dd = dxo + dy + dz;   // diag64
+                double be = (double)bc.e[p], bo = (double)bc.o[p];
+                if constexpr (REBASE) {
+                    be -= op64(g, hc.o[p], from_left(hc.o[p]), hs.e[p], hn.e[p], hc.e[p - 1], hc.e[p + 1], de, hc.e[p]);
+                    bo -= op64(g, hc.e[p], from_right(hc.e[p]), hs.o[p], hn.o[p], hc.o[p - 1], hc.o[p + 1], dd, hc.o[p]);
+                    const long long e = g.col(0, j, k);
+                    if (own && ok) poke(at(pick(odd, a.P.r0[1], a.P.r0[0]) + e, il), (float)be);
+                    if (own_o && ok) poke(at(pick(odd, a.P.r0[0], a.P.r0[1]) + e, il), (float)bo);
+                }
+                const double te = be - op64(g, dc.o[p], from_left(dc.o[p]), ds.e[p], dn.e[p], dc.e[p - 1], dc.e[p + 1], de, dc.e[p]);
+                const double to = bo - op64(g, dc.e[p], from_right(dc.e[p]), ds.o[p], dn.o[p], dc.o[p - 1], dc.o[p + 1], dd, dc.o[p]);
+                if (own && ok) s += te * te;
+                if (own_o && ok) s += to * to;
             }
         }
         if (REBASE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // r0 is out before the blocks meet: ghosts read it
@@ -603,7 +666,7 @@ struct Resident {
                         v[q] = __hip_atomic_load(gs + q * nb + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                         ok = ok && (unsigned)(v[q] >> 32) == gtag;
                     }
-                if (dead || __all(ok)) break;
+                if (__builtin_expect(dead || __all(ok), 1)) break;
                 if (spin >= kResSpin) dead = true;
             }
             if (need)
@@ -640,11 +703,19 @@ __global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(2, 
     const int K = a.K, max_iter = ctl->max_iter;
     const double tol = ctl->tol, rhs2 = ctl->rhs2;
     int m = ctl->m, left = a.cap, done = 0;
-    bool stored = false;
     long long cidx = m / K;
     double R = ctl->resid, reltmp2 = 0.0;
     typename Res::Step st{a.tag0, a.tag0, 0};
     unsigned gtag = a.tag0;
+    auto finish = [&](bool lost) {
+        if (lost && threadIdx.x == 0) ctl->pad_u[0] = 1;
+        if (w.t != 0 || threadIdx.x != 0) return;
+        ctl->m = m;
+        ctl->skip = 0;
+        ctl->resid = R;
+        ctl->reltmp2 = reltmp2;
+        ctl->done = done;
+    };
     auto publish1 = [&]() {   // colour 1's borders as they stand
         w.template publish<1>(st.tag, E, O);
         w.template pass<1>(st.tag, E, O);
@@ -681,27 +752,21 @@ __global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(2, 
             w.gather(++gtag, s, none);
             R = sqrt(s) / sqrt(rhs2);
             done = !isfinite(R) ? 3 : (R <= tol ? 1 : (m >= max_iter ? 2 : 0));
-            if (!done) {
-                w.template load<true>(w.live, a.P.pd, E, O);
-                w.load_r0(rE, rO);
-                ++st.tag;
-                st.age = 0;   // the ghosts came along
-                __syncthreads();
-                publish1();
-            }
+            // (a stop leaves here: pd is in memory, and the tile's registers are
+            // free in the residual)
+            if (done) return finish(__syncthreads_or(w.dead));
+            if (a.nbx > 1) w.load_ghosts(a.P.pd, E, O);
+            w.load_r0(rE, rO);
+            ++st.tag;
+            st.age = 0;   // the ghosts came along
+            __syncthreads();
+            publish1();
         }
         const bool lost = __syncthreads_or(w.dead);
-        if (lost && threadIdx.x == 0) ctl->pad_u[0] = 1;
-        stored = done != 0;   // a stop follows a check, which left pd in memory
-        if (done || left <= 0 || lost) break;
-    }
-    if (!stored) w.store(a.P.pd, E, O);
-    if (w.t == 0 && threadIdx.x == 0) {
-        ctl->m = m;
-        ctl->skip = 0;
-        ctl->resid = R;
-        ctl->reltmp2 = reltmp2;
-        ctl->done = done;
+        if (left <= 0 || lost) {
+            w.store(a.P.pd, E, O);
+            return finish(lost);
+        }
     }
 }
 
