@@ -2,18 +2,16 @@
 // alternative to the red-black scheme, built here as a measured comparison
 // solver beside the red-black SOR of the time step.
 //
-// p is held as a pair (p_0, p_1) per cell in one interleaved float2 array
-// with a zero ghost ring, natural order ((nz+2) planes of (ny+2) rows of
-// nx+2 pairs).  The first half of an iteration sets every cell's p_1 from
-// the p_0 values (own and six neighbours), the second half p_0 from p_1,
-// each with the SOR point formula (sor_point, the same rounding as the
-// red-black sweeps).  Every neighbour therefore comes from the previous
-// half: a relaxed Jacobi iteration, not red-black SOR.
+// p is held as a pair (p_0, p_1) per cell.  The first half of an iteration
+// sets every cell's p_1 from the p_0 values (own and six neighbours, 0 outside
+// the grid), the second half p_0 from p_1, each with the SOR point formula
+// (sor_nb, sor_relax: the same rounding as the red-black sweeps).  Every
+// neighbour therefore comes from the previous half: a relaxed Jacobi
+// iteration, not red-black SOR.
 //
-// 64 consecutive cells of a row per wavefront, 4 rows per block, each
-// thread marching up 8 planes of its column.  Per half: the pair of the
-// cell (8 bytes; neighbours from registers, lanes and the cache), rhs (4
-// bytes) and one component written (4 bytes), 16 bytes per cell at best.
+// One kernel per iteration: p_1 lives in registers only, and p_0 goes from one
+// array to another, so an iteration moves 12 bytes per cell at best (p_0 and
+// rhs read, p_0 written).  See k_twin_iter.
 #include <algorithm>
 #include <cmath>
 #include <cstdio>
@@ -25,101 +23,202 @@ using namespace les;
 
 namespace {
 
-constexpr int kTwRows = kBlock / 64;
+constexpr int kTwRows = 2;                  // rows of a wavefront
+constexpr int kTwWaves = kBlock / 64;
+constexpr int kTwSpan = 2 * 62;             // cells of a row per wavefront: 64 lanes x 2, one lane a side recomputed
+constexpr int kTwPlanesMax = 15;
+constexpr long long kTwMinWaves = 1536;
 
-__device__ __forceinline__ long long tw_index(const Geo& g, int i0, int j0, int k0) {
-    return ((long long)(k0 + 1) * (g.ny + 2) + (j0 + 1)) * (g.nx + 2) + (i0 + 1);
+// Two cells of a row, 4-byte aligned (rows of odd length).
+struct __attribute__((packed, aligned(4))) TwPair {
+    float x, y;
+};
+__device__ __forceinline__ float tw_left(float v) {    // lane l takes lane l - 1's v (lane 0: 0)
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x138, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float tw_right(float v) {   // lane l takes lane l + 1's v (lane 63: 0)
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
 }
 
-__device__ __forceinline__ bool tw_cell(const Geo& g, int& i0, int& j0, int& k0) {
-    i0 = (int)blockIdx.x * 64 + (int)(threadIdx.x & 63);
-    j0 = (int)blockIdx.y * kTwRows + (int)(threadIdx.x >> 6);
-    k0 = (int)blockIdx.z;
-    return i0 < g.nx && j0 < g.ny;
-}
-
-__global__ __launch_bounds__(kBlock) void k_twin_load(Geo g, const float* __restrict__ p,
-                                                      float2* __restrict__ q) {
-    int i0, j0, k0;
-    if (!tw_cell(g, i0, j0, k0)) return;
-    const float v = p[((long long)k0 * g.ny + j0) * g.nx + i0];
-    q[tw_index(g, i0, j0, k0)] = make_float2(v, v);
-}
-
-// Half-iteration: component SRC of every cell's pair -> component 1 - SRC.
-// A thread marches up kt planes of its (i, j) column keeping the values of
-// planes k-1, k, k+1 in registers; east and west come from the adjacent
-// lanes (a wavefront holds 64 consecutive cells of a row), the row ends and
-// the last cell of the grid row from memory.  Lanes past the row end take
-// part in the shuffles only.
-// kt: at most 8, fewer when the grid would otherwise have under 1024
-// blocks (4 per compute unit; measured: at 150x150x90, 8 planes in 1368
-// blocks beat 2 planes in 5130).
-constexpr int kTwPlanesMax = 8;
-constexpr long long kTwMinBlocks = 1024;
-
-template <int SRC>
-__global__ __launch_bounds__(kBlock) void k_twin_sweep(Geo g, float2* q, const float* __restrict__ rhs,
-                                                       float omega, int kt) {
+// One iteration, src -> dst (both halves).  A wavefront holds two cells per
+// lane of kTwRows rows and marches up its planes: with p_0 of three planes and
+// kTwRows + 4 rows in registers it forms p_1 one plane ahead on kTwRows + 2
+// rows, and from three planes of that the new p_0.  Rows, planes and the one
+// lane on either side that a neighbouring wavefront owns are computed twice,
+// so that wavefronts need nothing of each other; x neighbours come from the
+// lanes.  The next plane is loaded while one is computed.
+// An iteration of 300x300x90 takes 32 us (two sweeps over interleaved pairs,
+// 28 to 40 bytes per cell with the half-written lines: 98 us), of 150x150x90 14
+// us, of 64x64x32 5.5 us.  12 bytes per cell take 12 us at 300x300x90 at the
+// rate of a copy that stays in the Infinity Cache; the rest is the
+// chain of a march, 1.8 us per step, with 19 steps to 15 planes.  Four rows per
+// wavefront read less twice but leave fewer wavefronts: 31, 18 and 6.7 us;
+// six: 49, 23 and 7.8.
+template <bool ODD>
+__global__ __launch_bounds__(kBlock) void k_twin_iter(Geo g, const float* __restrict__ src, const float* __restrict__ rhs,
+                                                      float* __restrict__ dst, float omega, int nseg, int span, int nyb, int kt) {
+    constexpr int RY = kTwRows, R0 = RY + 4, R1 = RY + 2;   // rows of p_0, p_1
     const int lane = (int)(threadIdx.x & 63);
-    const int i0 = (int)blockIdx.x * 64 + lane;
-    const int j0 = (int)blockIdx.y * kTwRows + (int)(threadIdx.x >> 6);
-    if (j0 >= g.ny) return;                      // a whole wavefront
-    const int kb = (int)blockIdx.z * kt;
-    const int ke = min(g.nz, kb + kt);
-    const bool live = i0 < g.nx;
-    const float* src = reinterpret_cast<const float*>(q) + SRC;
-    float* dst = reinterpret_cast<float*>(q) + (1 - SRC);
-    const long long X = g.nx + 2, P = X * (g.ny + 2);
-    long long e = tw_index(g, i0, j0, kb);
-    const long long rrow = (long long)j0 * g.nx + i0, rplane = (long long)g.ny * g.nx;
-    const float dxy = diag_x(g, i0) + diag_y(g, j0);
-    float pb = live ? src[2 * (e - P)] : 0.f;
-    float pc = live ? src[2 * e] : 0.f;
-    for (int k0 = kb; k0 < ke; ++k0) {
-        const float pt = live ? src[2 * (e + P)] : 0.f;
-        float pe = __shfl_down(pc, 1, 64);
-        float pw = __shfl_up(pc, 1, 64);
-        if (live) {
-            if (lane == 63 || i0 == g.nx - 1) pe = src[2 * (e + 1)];
-            if (lane == 0) pw = src[2 * (e - 1)];
-            const float ps = src[2 * (e - X)], pn = src[2 * (e + X)];
-            const float r = rhs[(long long)k0 * rplane + rrow];
-            float reltmp;
-            dst[2 * e] = sor_point(pw, pe, ps, pn, pb, pt, g.cx, g.cy, g.cz, dxy + diag_z(g, k0), r, pc,
-                                   omega, reltmp);
+    const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lb = (int)xcd_block(blockIdx.x, gridDim.x);
+    auto uni = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+    const int seg = uni(lb % nseg), yb = uni((lb / nseg) % nyb), zb = uni(lb / (nseg * nyb));
+    const int j0 = (yb * kTwWaves + wv) * RY;
+    if (j0 >= g.ny) return;   // a whole wavefront
+    const int kb = zb * kt, ke = min(g.nz, kb + kt);
+    const int i = seg * span - 2 + 2 * lane;   // the lane's cells: i, i + 1
+    const bool in_e = i >= 0 && i < g.nx, in_o = i + 1 >= 0 && i + 1 < g.nx;
+    const bool last = i == g.nx - 1;           // the row's last cell, alone
+    const int ic = min(max(i, 0), g.nx - 2);
+    const bool own = lane > 0 && 2 * (lane - 1) < span && in_e;
+    const long long sx = g.nx, sp = sx * g.ny;
+    // 1 / diagonal of the lane's cells: [inside or on the grid's outer rows]
+    struct Inv {
+        float e[2], o[2];
+    };
+    Inv inner, outer;   // on inner and outer planes
+#pragma unroll
+    for (int ye = 0; ye < 2; ++ye) {
+        const float dy = ye ? diag_y(g, 0) : g.cy + g.cy;
+        const float de = diag_x(g, i) + dy, dd = diag_x(g, i + 1) + dy;
+        inner.e[ye] = 1.0f / (de + (g.cz + g.cz));
+        inner.o[ye] = 1.0f / (dd + (g.cz + g.cz));
+        outer.e[ye] = 1.0f / (de + diag_z(g, 0));
+        outer.o[ye] = 1.0f / (dd + diag_z(g, 0));
+    }
+    auto pick = [](bool c, float x, float y) { return c ? x : y; };
+    struct Plane0 {
+        float e[R0], o[R0];
+    };
+    struct Plane1 {
+        float e[R1], o[R1];
+    };
+    // n rows of plane k from row j, as loaded (outside the grid its nearest row
+    // and plane); trim() then clears what is outside
+    auto fetch = [&](const float* q, int j, int k, auto& p, int n) {
+        k = min(max(k, 0), g.nz - 1);
+#pragma unroll
+        for (int r = 0; r < n; ++r) {
+            const TwPair v = *(const TwPair*)(q + (k * sp + min(max(j + r, 0), g.ny - 1) * sx) + ic);
+            p.e[r] = v.x;
+            p.o[r] = v.y;
         }
-        pb = pc;
-        pc = pt;
-        e += P;
+    };
+    auto trim = [&](int j, int k, auto& p, int n) {
+        const bool ok = k >= 0 && k < g.nz;
+#pragma unroll
+        for (int r = 0; r < n; ++r) {
+            const bool row = ok && j + r >= 0 && j + r < g.ny;
+            p.e[r] = in_e && row ? (ODD && last ? p.o[r] : p.e[r]) : 0.f;
+            p.o[r] = in_o && row ? p.o[r] : 0.f;
+        }
+    };
+    // one half at a pair of row j from the values around it
+    auto half = [&](int j, const Inv& d, float e, float o, float se, float so, float ne, float no, float be, float bo, float te,
+                    float to, float re, float ro, float& xe, float& xo) {
+        const bool ye = j == 0 || j == g.ny - 1;
+        float rt;
+        xe = sor_relax(sor_nb(tw_left(o), o, se, ne, be, te, g.cx, g.cy, g.cz), pick(ye, d.e[1], d.e[0]), re, e, omega, rt);
+        xo = sor_relax(sor_nb(e, tw_right(e), so, no, bo, to, g.cx, g.cy, g.cz), pick(ye, d.o[1], d.o[0]), ro, o, omega, rt);
+    };
+    auto inv_of = [&](int k) {
+        const bool ze = k == 0 || k == g.nz - 1;
+        Inv d;
+#pragma unroll
+        for (int ye = 0; ye < 2; ++ye) {
+            d.e[ye] = pick(ze, outer.e[ye], inner.e[ye]);
+            d.o[ye] = pick(ze, outer.o[ye], inner.o[ye]);
+        }
+        return d;
+    };
+    // Step k: p_1 on plane k + 1 (b2) from p_0 on k .. k + 2 (a0 .. a2), then the
+    // new p_0 on plane k from p_1 on k - 1 .. k + 1; a3 and f2 come in meanwhile.
+    auto step = [&](int k, const Plane0& a0, const Plane0& a1, const Plane0& a2, Plane0& a3, const Plane1& b0, const Plane1& b1,
+                    Plane1& b2, const Plane1& f0, const Plane1& f1, Plane1& f2) {
+        fetch(src, j0 - 2, k + 3, a3, R0);
+        fetch(rhs, j0 - 1, k + 2, f2, R1);
+        const Inv d1 = inv_of(k + 1), d0 = inv_of(k);
+#pragma unroll
+        for (int r = 0; r < R1; ++r) {
+            const int j = j0 - 1 + r;
+            float e, o;
+            half(j, d1, a1.e[r + 1], a1.o[r + 1], a1.e[r], a1.o[r], a1.e[r + 2], a1.o[r + 2], a0.e[r + 1], a0.o[r + 1],
+                 a2.e[r + 1], a2.o[r + 1], f1.e[r], f1.o[r], e, o);
+            const bool row = k + 1 >= 0 && k + 1 < g.nz && j >= 0 && j < g.ny;
+            b2.e[r] = in_e && row ? e : 0.f;
+            b2.o[r] = in_o && row ? o : 0.f;
+        }
+        if (k >= kb) {
+            TwPair v[RY];
+#pragma unroll
+            for (int r = 1; r <= RY; ++r)
+                half(j0 - 1 + r, d0, b1.e[r], b1.o[r], b1.e[r - 1], b1.o[r - 1], b1.e[r + 1], b1.o[r + 1], b0.e[r], b0.o[r],
+                     b2.e[r], b2.o[r], f0.e[r], f0.o[r], v[r - 1].x, v[r - 1].y);
+            float* q = dst + (k * sp + j0 * sx) + i;
+#pragma unroll
+            for (int r = 0; r < RY; ++r)
+                if (j0 + r < g.ny) {
+                    if (own && in_o) *(TwPair*)(q + r * sx) = v[r];
+                    else if (ODD && own) q[r * sx] = v[r].x;
+                }
+        }
+        trim(j0 - 2, k + 3, a3, R0);
+        trim(j0 - 1, k + 2, f2, R1);
+    };
+    Plane0 a0, a1, a2, a3;
+    Plane1 b0{}, b1{}, b2, b3, f0{}, f1, f2, f3;
+    fetch(src, j0 - 2, kb - 2, a0, R0);
+    fetch(src, j0 - 2, kb - 1, a1, R0);
+    fetch(src, j0 - 2, kb, a2, R0);
+    fetch(rhs, j0 - 1, kb - 1, f1, R1);
+    trim(j0 - 2, kb - 2, a0, R0);
+    trim(j0 - 2, kb - 1, a1, R0);
+    trim(j0 - 2, kb, a2, R0);
+    trim(j0 - 1, kb - 1, f1, R1);
+    // four steps a turn, so that the planes stay in their registers
+#pragma unroll 1
+    for (int k = kb - 2;; k += 4) {
+        step(k, a0, a1, a2, a3, b0, b1, b2, f0, f1, f2);
+        if (k + 1 >= ke) break;
+        step(k + 1, a1, a2, a3, a0, b1, b2, b3, f1, f2, f3);
+        if (k + 2 >= ke) break;
+        step(k + 2, a2, a3, a0, a1, b2, b3, b0, f2, f3, f0);
+        if (k + 3 >= ke) break;
+        step(k + 3, a3, a0, a1, a2, b3, b0, b1, f3, f0, f1);
+        if (k + 4 >= ke) break;
     }
 }
 
-__global__ __launch_bounds__(kBlock) void k_twin_store(Geo g, const float2* __restrict__ q,
-                                                       float* __restrict__ p) {
-    int i0, j0, k0;
-    if (!tw_cell(g, i0, j0, k0)) return;
-    p[((long long)k0 * g.ny + j0) * g.nx + i0] = q[tw_index(g, i0, j0, k0)].x;
+__global__ __launch_bounds__(kBlock) void k_twin_copy(const float* __restrict__ src, float* __restrict__ dst, long long n) {
+    for (long long e = (long long)blockIdx.x * kBlock + threadIdx.x; e < n; e += (long long)gridDim.x * kBlock) dst[e] = src[e];
 }
 
 // Per-block float64 partials of sum (rhs - A p_0)^2 and sum rhs^2, A p =
 // sum_nb cn_nb p_nb - diag p, elementwise in float64 from the float32
-// values; fixed order within the block.
-__global__ __launch_bounds__(kBlock) void k_twin_resid(Geo g, const float2* __restrict__ q,
+// values; fixed order within the block.  A thread marches up 16 planes of its
+// column (one cell per thread left tens of thousands of partials to copy and
+// add on the host).
+constexpr int kTwResidPlanes = 16;
+__global__ __launch_bounds__(kBlock) void k_twin_resid(Geo g, const float* __restrict__ p,
                                                        const float* __restrict__ rhs,
                                                        double* __restrict__ part) {
-    int i0, j0, k0;
+    const int i0 = (int)blockIdx.x * 64 + (int)(threadIdx.x & 63);
+    const int j0 = (int)blockIdx.y * kTwWaves + (int)(threadIdx.x >> 6);
+    const int kb = (int)blockIdx.z * kTwResidPlanes, ke = min(g.nz, kb + kTwResidPlanes);
     double r2 = 0.0, b2 = 0.0;
-    if (tw_cell(g, i0, j0, k0)) {
-        const long long e = tw_index(g, i0, j0, k0);
-        const long long X = g.nx + 2, P = X * (g.ny + 2);
-        const double nb = (double)g.cx * ((double)q[e - 1].x + (double)q[e + 1].x) +
-                          (double)g.cy * ((double)q[e - X].x + (double)q[e + X].x) +
-                          (double)g.cz * ((double)q[e - P].x + (double)q[e + P].x);
-        const double ap = nb - (double)diag_of(g, i0, j0, k0) * (double)q[e].x;
-        const double b = (double)rhs[((long long)k0 * g.ny + j0) * g.nx + i0];
-        r2 = (b - ap) * (b - ap);
-        b2 = b * b;
+    if (i0 < g.nx && j0 < g.ny) {
+        const long long X = g.nx, P = X * g.ny;
+        for (int k0 = kb; k0 < ke; ++k0) {
+            const long long e = k0 * P + j0 * X + i0;
+            auto at = [&](bool in, long long d) { return in ? (double)p[e + d] : 0.0; };
+            const double nb = (double)g.cx * (at(i0 > 0, -1) + at(i0 < g.nx - 1, 1)) +
+                              (double)g.cy * (at(j0 > 0, -X) + at(j0 < g.ny - 1, X)) +
+                              (double)g.cz * (at(k0 > 0, -P) + at(k0 < g.nz - 1, P));
+            const double ap = nb - (double)diag_of(g, i0, j0, k0) * (double)p[e];
+            const double b = (double)rhs[e];
+            r2 += (b - ap) * (b - ap);
+            b2 += b * b;
+        }
     }
     const long long lb = ((long long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const double s = block_sum(r2);
@@ -158,20 +257,17 @@ extern "C" int les_pressure_solve_twinned(les_handle* h, const float* d_rhs, flo
     if (!(omega > 0.0 && omega <= 1.0)) return tw_err(h, LES_EINVAL, "omega outside (0, 1]");
     if (h->g.stretched) return tw_err(h, LES_EINVAL, "uniform grids only");
     const Geo& g = h->g;
-    const dim3 grid((unsigned)((g.nx + 63) / 64), (unsigned)((g.ny + kTwRows - 1) / kTwRows),
-                    (unsigned)g.nz);
+    const long long n = (long long)g.nx * g.ny * g.nz;
+    const dim3 grid((unsigned)((g.nx + 63) / 64), (unsigned)((g.ny + kTwWaves - 1) / kTwWaves),
+                    (unsigned)((g.nz + kTwResidPlanes - 1) / kTwResidPlanes));
     const size_t nblocks = (size_t)grid.x * grid.y * grid.z;
     hipStream_t s = stream ? (hipStream_t)stream : h->stream;
     if (!h->tw_q) {
-        // installed in the handle only once both buffers exist and the
-        // ghost ring is zero
-        const size_t npair = (size_t)(g.nx + 2) * (g.ny + 2) * (g.nz + 2);
+        // installed in the handle only once both buffers exist
         void* qa = nullptr;
         void* pa = nullptr;
-        hipError_t e = hipMalloc(&qa, npair * sizeof(float2));
+        hipError_t e = hipMalloc(&qa, 2 * n * sizeof(float));
         if (e == hipSuccess) e = hipMalloc(&pa, 2 * nblocks * sizeof(double));
-        if (e == hipSuccess) e = hipMemsetAsync(qa, 0, npair * sizeof(float2), s);
-        if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (e != hipSuccess) {
             if (qa) (void)hipFree(qa);
             if (pa) (void)hipFree(pa);
@@ -180,12 +276,19 @@ extern "C" int les_pressure_solve_twinned(les_handle* h, const float* d_rhs, flo
         h->tw_q = qa;
         h->tw_part = (double*)pa;
     }
-    float2* q = (float2*)h->tw_q;
+    float* q[2] = {(float*)h->tw_q, (float*)h->tw_q + n};
     double* part = h->tw_part;
     const dim3 block(kBlock);
-    const long long per_plane = (long long)grid.x * grid.y;
-    int kt = (int)std::min<long long>(kTwPlanesMax, std::max<long long>(1, (long long)g.nz * per_plane / kTwMinBlocks));
-    const dim3 sweep_grid(grid.x, grid.y, (unsigned)((g.nz + kt - 1) / kt));
+    // rows in as few spans as cover them, even and as long as each other
+    const int nseg = (g.nx + kTwSpan - 1) / kTwSpan, span = ((g.nx + nseg - 1) / nseg + 1) & ~1;
+    const int nyb = (g.ny + kTwWaves * kTwRows - 1) / (kTwWaves * kTwRows);
+    // Planes of a wavefront: a march reads four planes beyond its own, so the
+    // longest one that leaves 1536 wavefronts (1.5 per SIMD), and at most 15:
+    // 150x150x90 took 14.1 us this way, 17.9 with 1024 wavefronts, 19.0 with
+    // 4096; 300x300x90 31.6 us with 15 planes, 35.4 with 8, 33.7 with 30.
+    const long long columns = (long long)nseg * nyb * kTwWaves;
+    const int kt = (int)std::min<long long>(kTwPlanesMax, std::max<long long>(1, g.nz * columns / kTwMinWaves));
+    const dim3 iter_grid((unsigned)(nseg * nyb) * (unsigned)((g.nz + kt - 1) / kt));
     hipEvent_t ev[2] = {nullptr, nullptr};
     auto fin = [&](int rc) {
         for (auto& e : ev)
@@ -194,18 +297,22 @@ extern "C" int les_pressure_solve_twinned(les_handle* h, const float* d_rhs, flo
     };
     for (auto& e : ev)
         if (hipEventCreate(&e) != hipSuccess) return fin(tw_err(h, LES_EDEVICE, "hipEventCreate"));
-    hipLaunchKernelGGL(k_twin_load, grid, block, 0, s, g, d_p, q);
-    if (hipGetLastError() != hipSuccess) return fin(tw_err(h, LES_EDEVICE, "k_twin_load"));
     if (hipEventRecord(ev[0], s) != hipSuccess) return fin(tw_err(h, LES_EDEVICE, "event"));
     const float om = (float)omega;
+    // d_p -> q[0] -> q[1] -> ... -> d_p; the last into q where d_p is still
+    // read by it (one iteration) or is (part of) the right-hand side
+    const bool apart = d_p + n <= d_rhs || d_rhs + n <= d_p;
+    const auto iter = (g.nx & 1) ? k_twin_iter<true> : k_twin_iter<false>;
+    const float* from = d_p;
     for (int m = 0; m < iters; ++m) {
-        hipLaunchKernelGGL(k_twin_sweep<0>, sweep_grid, block, 0, s, g, q, d_rhs, om, kt);
-        hipLaunchKernelGGL(k_twin_sweep<1>, sweep_grid, block, 0, s, g, q, d_rhs, om, kt);
+        float* to = m > 0 && m == iters - 1 && apart ? d_p : q[m & 1];
+        hipLaunchKernelGGL(iter, iter_grid, block, 0, s, g, from, d_rhs, to, om, nseg, span, nyb, kt);
+        from = to;
     }
-    if (hipGetLastError() != hipSuccess) return fin(tw_err(h, LES_EDEVICE, "k_twin_sweep"));
+    if (hipGetLastError() != hipSuccess) return fin(tw_err(h, LES_EDEVICE, "k_twin_iter"));
     if (hipEventRecord(ev[1], s) != hipSuccess) return fin(tw_err(h, LES_EDEVICE, "event"));
-    hipLaunchKernelGGL(k_twin_store, grid, block, 0, s, g, q, d_p);
-    hipLaunchKernelGGL(k_twin_resid, grid, block, 0, s, g, q, d_rhs, part);
+    if (from != d_p) hipLaunchKernelGGL(k_twin_copy, dim3(1024), block, 0, s, from, d_p, n);
+    hipLaunchKernelGGL(k_twin_resid, grid, block, 0, s, g, d_p, d_rhs, part);
     if (hipGetLastError() != hipSuccess) return fin(tw_err(h, LES_EDEVICE, "k_twin_resid"));
     std::vector<double> hp(2 * nblocks);
     hipError_t e = hipMemcpyAsync(hp.data(), part, hp.size() * sizeof(double), hipMemcpyDeviceToHost, s);
