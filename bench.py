@@ -21,6 +21,8 @@ Prints ONE JSON line:
              written and own r0 read (12 B per cell of this colour).
              `traffic` is the measured HBM bytes (rocprofv3 FETCH_SIZE +
              WRITE_SIZE, copy-calibrated) from the summaries in profiles/.
+             Where the autotuner keeps the resident solver, its flops
+             (13 per cell and iteration) against the vector units.
   cpu_baseline  the FP64 oracle on the host cores, on a bounded sample
 
 Other modes print their own JSON line: --ensemble N, --warm-start,
@@ -135,7 +137,8 @@ def omega_study(les, torch, w, mask, g, variant, omega, K, steps=2):
     rows = []
     try:
         t.set_state(blob)
-        t.set_sor_variant(variant)
+        if variant is not None:
+            t.set_sor_variant(variant)
         for _ in range(steps):
             torch.cuda.synchronize()
             t0 = time.perf_counter()
@@ -152,6 +155,8 @@ def omega_study(les, torch, w, mask, g, variant, omega, K, steps=2):
             "ms_per_step": sum(r["ms"] for r in rows) / len(rows)}
 
 
+VALU_F32_PEAK_TFLOPS = 78.6      # MI355X vector FP32 without packed instructions: half the vendor figure
+SOR_FLOPS = 13                   # per cell and iteration: sor_nb 8, sor_relax 5
 MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense BF16 matrix peak, vendor figure
 
 
@@ -432,7 +437,7 @@ def bench_twinned(args, les, torch):
             torch.cuda.synchronize()
             ms_rb = (time.perf_counter() - t0) * 1e3
             best_rb = ms_rb if best_rb is None else min(best_rb, ms_rb)
-        tw_bytes = 32.0 * cells * n            # per half: pair 8 B + rhs 4 B + one component 4 B
+        tw_bytes = 12.0 * cells * n            # per iteration: p_0 read and written, rhs read
         rows.append({"iters": n,
                      "twinned": {"resid": st_tw["resid"], "ms": best_tw, "us_per_iter": 1e3 * best_tw / n,
                                  "GB_per_s": tw_bytes / (best_tw * 1e-3) / 1e9,
@@ -671,7 +676,19 @@ def main():
         },
     }
     sor_ms, sor_n = timing["sor"]
-    if sor_n > 0:
+    # the resident solver times every iteration, checks and folds included; the
+    # sweep launches are sampled (one check interval in eight)
+    resident = args.sor_variant is None and sor_n > 0 and sor_n == int(iters.sum())
+    if resident:
+        t_iter = sor_ms / sor_n * 1e-3
+        tf = SOR_FLOPS * cells / t_iter / 1e12
+        # pd and r0 stay in registers and LDS: neither memory nor a cache bounds
+        # an iteration, but the vector units and the exchange between tiles
+        out["roofline"] = {"bound": "valu", "kernel": "k_resident (whole solves, checks and folds included)",
+                           "achieved": tf, "peak": VALU_F32_PEAK_TFLOPS, "unit": "TFLOP/s",
+                           "frac": tf / VALU_F32_PEAK_TFLOPS, "us_per_iteration": t_iter * 1e6,
+                           "flops_per_cell_iteration": SOR_FLOPS, "timed_iterations": int(sor_n)}
+    elif sor_n > 0:
         t_launch = sor_ms / sor_n * 1e-3
         fused = variant >= les.NUM_SPLIT_SOR_VARIANTS
         two = variant >= les.FIRST_TWO_ITER_SOR_VARIANT
@@ -722,6 +739,7 @@ def main():
             "min_bytes_frac": min_bytes_per_launch / t_launch / 1e9 / HBM_PEAK_GBS,
             "timed_launches": int(sor_n),
         }
+    if sor_n > 0:
         out["kernel_ms_per_step"] = {k: v[0] / args.steps for k, v in timing.items()
                                      if v[1] > 0 and k not in ("sor", "check")}
         # the residual checks are sampled with the sweeps (one interval in 8):
@@ -730,7 +748,7 @@ def main():
         if chk_n > 0:
             out["kernel_ms_per_step"]["check"] = chk_ms / chk_n * float(iters.mean()) / K
         # the SOR sweeps are sampled (one check interval in 8): scale to all
-        out["kernel_ms_per_step"]["sor"] = (sor_ms / sor_n) / iters_per_launch * float(iters.mean())
+        out["kernel_ms_per_step"]["sor"] = (sor_ms / sor_n) / (1 if resident else iters_per_launch) * float(iters.mean())
         # device time of the pressure solve per timed step (sweeps, stopping
         # tests, fold and rebase), whether or not the steps converged
         out["solve_kernel_ms_per_step"] = (out["kernel_ms_per_step"]["sor"]
@@ -738,7 +756,7 @@ def main():
                                            + out["kernel_ms_per_step"].get("rebase", 0.0))
     if not args.no_omega_study:
         log("omega study: Young's relaxation factor from the timed state")
-        out["omega_study"] = omega_study(les, torch, w, mask, g, variant, young_omega(w), K)
+        out["omega_study"] = omega_study(les, torch, w, mask, g, None if resident else variant, young_omega(w), K)
     if not args.no_net:
         log("warm-start network: forward and train step on a 64x128x128 crop")
         out["warm_start_net"] = bench_net(les, torch)
