@@ -1299,8 +1299,9 @@ __device__ __forceinline__ double diag64(const Geo& g, int i0, int j0, int k0) {
         return dx + dy + dz;
     }
 }
-// (A x) of a uniform-grid cell with value x and diagonal d; the order of the
-// products is pinned, so that every kernel rounds alike.
+// (A x) of a uniform-grid cell with value x and diagonal d, rounded as the
+// compiler contracts apply_A64's uniform branch (the resident solver's values
+// are compared with the sweeps' bit for bit).
 __device__ __forceinline__ double op64(const Geo& g, float west, float east, float south, float north, float below,
                                        float above, double d, float x) {
     const double nb = fma(g.czd, (double)below + (double)above,
@@ -1320,7 +1321,10 @@ __device__ __forceinline__ double apply_A64(const Geo& g, const float* xo, const
                           wrow(g.wz, g.nz, 1, k0 + 1) * (double)xn[e + g.SP];
         return nb - d * (double)xo[e];
     } else {
-        return op64(g, xn[e - 1 + s], xn[e + s], xn[e - g.S], xn[e + g.S], xn[e - g.SP], xn[e + g.SP], d, xo[e]);
+        const double nb = g.cxd * ((double)xn[e - 1 + s] + (double)xn[e + s]) +
+                          g.cyd * ((double)xn[e - g.S] + (double)xn[e + g.S]) +
+                          g.czd * ((double)xn[e - g.SP] + (double)xn[e + g.SP]);
+        return nb - d * (double)xo[e];
     }
 }
 
