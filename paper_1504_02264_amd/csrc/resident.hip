@@ -297,10 +297,10 @@ struct Resident {
     static __device__ __forceinline__ u64 get(const u64* p) {
         return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // Renew the ghost columns (refresh number n): a tile's first and last g
-    // columns, both colours, go to its x neighbours; a flag follows the columns
-    // once they are at the point of coherence.  Patches pair one to one, so two
-    // sets of words suffice.
+    // Renew the ghost columns (event number n): a tile's first and last g
+    // columns, both colours, go to its x neighbours; the event's flag follows the
+    // columns once they are at the point of coherence.  Patches pair one to one,
+    // so two sets of words suffice.
     __device__ __forceinline__ void refresh(unsigned n, Patch& E, Patch& O) {
         const int g = first;
         auto column = [&](unsigned tile, int side, int l) {
@@ -314,19 +314,8 @@ struct Resident {
                 __hip_atomic_store(p + q * g, ((u64)__float_as_uint(O[q / RZ][q % RZ]) << 32) | __float_as_uint(E[q / RZ][q % RZ]),
                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        if (lane == 0)
-            __hip_atomic_store(a.xflag + (t * kResWaves + wv) * kResPad, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool see = (lane == 0 && west) || (lane == 1 && east);
-        const unsigned* flag = a.xflag + ((lane ? t + 1 : t - 1) * kResWaves + wv) * kResPad;
-#pragma unroll 1
-        for (int spin = 0;; ++spin) {   // a neighbour may be one refresh ahead
-            bool ok = true;
-            if (see) ok = (int)(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - n) >= 0;
-            if (__builtin_expect(dead || __all(ok), 1)) break;
-            if (spin >= kResSpin) dead = true;
-        }
-        asm volatile("" ::: "memory");   // no column before its flag
+        reach(n);
+        meet(n);
         const bool gw = west && lane < g, ge = east && lane > last && lane <= last + g;
         if (gw || ge) {
             const u64* p = column(gw ? t - 1 : t + 1, gw ? 1 : 0, gw ? lane : lane - last - 1);
@@ -338,6 +327,26 @@ struct Resident {
                 O[q / RZ][q % RZ] = __uint_as_float((unsigned)(v >> 32));
             }
         }
+    }
+    // Event n of this patch, for its x neighbours: its columns are out, or it has
+    // read its ghosts from memory.  Every load and store before it is done.
+    __device__ __forceinline__ void reach(unsigned n) const {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if (lane == 0)
+            __hip_atomic_store(a.xflag + (t * kResWaves + wv) * kResPad, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // Both x neighbours have reached event n too (one may be an event ahead).
+    __device__ __forceinline__ void meet(unsigned n) {
+        const bool see = (lane == 0 && west) || (lane == 1 && east);
+        const unsigned* flag = a.xflag + ((lane ? t + 1 : t - 1) * kResWaves + wv) * kResPad;
+#pragma unroll 1
+        for (int spin = 0;; ++spin) {
+            bool ok = true;
+            if (see) ok = (int)(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - n) >= 0;
+            if (__builtin_expect(dead || __all(ok), 1)) break;
+            if (spin >= kResSpin) dead = true;
+        }
+        asm volatile("" ::: "memory");   // nothing that follows comes before the flags
     }
     // Fetch the neighbouring tiles' rows and planes of publication `tag` into
     // the halo: one wait for all words of the wavefront (a patch touches at most
@@ -458,7 +467,7 @@ struct Resident {
     // iterations; they are renewed before the last half-sweep's borders leave,
     // which then carry them.
     struct Step {
-        unsigned tag, refresh;
+        unsigned tag, event;   // last publication, last event among x neighbours
         int age;
     };
     template <int F>
@@ -468,7 +477,7 @@ struct Resident {
         halos(st.tag);
         relax<F, true>(acc, E, O, rE, rO, st.tag, r2, d2);
         if (F == 1 && a.nbx > 1 && ++st.age == first) {
-            refresh(++st.refresh, E, O);
+            refresh(++st.event, E, O);
             st.age = 0;
         }
         ++st.tag;
@@ -700,12 +709,13 @@ __global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(2, 
     w.load_r0(rE, rO);
     for (int q = threadIdx.x; q < (int)(sizeof sm.halo / sizeof(float)); q += kResThreads) (&sm.halo[0][0][0][0])[q] = 0.f;
     __syncthreads();
+    typename Res::Step st{a.tag0, a.tag0, 0};
+    if (a.nbx > 1) w.reach(++st.event);   // the ghosts are read
     const int K = a.K, max_iter = ctl->max_iter;
     const double tol = ctl->tol, rhs2 = ctl->rhs2;
     int m = ctl->m, left = a.cap, done = 0;
     long long cidx = m / K;
     double R = ctl->resid, reltmp2 = 0.0;
-    typename Res::Step st{a.tag0, a.tag0, 0};
     unsigned gtag = a.tag0;
     auto finish = [&](bool lost) {
         if (lost && threadIdx.x == 0) ctl->pad_u[0] = 1;
@@ -739,8 +749,14 @@ __global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(2, 
             check = !(m < max_iter && lbd > 1.5 * tol);
         }
         if (check) {
-            if (due) w.template leave<true>(E, O);
-            else w.template leave<false>(E, O);
+            // pd in memory may still be read as ghosts: the other intervals have
+            // met over the bound's sums since, a fold waits for its x neighbours
+            if (due) {
+                if (a.nbx > 1) w.meet(st.event);
+                w.template leave<true>(E, O);
+            } else {
+                w.template leave<false>(E, O);
+            }
             double meet = 0.0;
             if (due) {
                 w.gather(++gtag, meet, r2);
@@ -755,7 +771,10 @@ __global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(2, 
             // (a stop leaves here: pd is in memory, and the tile's registers are
             // free in the residual)
             if (done) return finish(__syncthreads_or(w.dead));
-            if (a.nbx > 1) w.load_ghosts(a.P.pd, E, O);
+            if (a.nbx > 1) {
+                w.load_ghosts(a.P.pd, E, O);
+                w.reach(++st.event);
+            }
             w.load_r0(rE, rO);
             ++st.tag;
             st.age = 0;   // the ghosts came along
