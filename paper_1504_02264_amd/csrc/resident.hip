@@ -335,14 +335,16 @@ struct Resident {
         if (lane == 0)
             __hip_atomic_store(a.xflag + (t * kResWaves + wv) * kResPad, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // Both x neighbours have reached event n too (one may be an event ahead).
+    // Both x neighbours have reached event n too.  One may be an event ahead, no
+    // more (the next needs this patch), so only n and n + 1 count: a flag left by
+    // an earlier launch, however old, or a cleared one is neither.
     __device__ __forceinline__ void meet(unsigned n) {
         const bool see = (lane == 0 && west) || (lane == 1 && east);
         const unsigned* flag = a.xflag + ((lane ? t + 1 : t - 1) * kResWaves + wv) * kResPad;
 #pragma unroll 1
         for (int spin = 0;; ++spin) {
             bool ok = true;
-            if (see) ok = (int)(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - n) >= 0;
+            if (see) ok = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - n <= 1u;
             if (__builtin_expect(dead || __all(ok), 1)) break;
             if (spin >= kResSpin) dead = true;
         }

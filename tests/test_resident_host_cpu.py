@@ -47,3 +47,11 @@ def test_order_of_tiles_in_a_row(exe, shape, K, R, max_iter, tol):
 def test_order_of_tiles_in_rows_and_planes(exe):
     out = lines(exe, (30, 9, 9), 4, 32, 12, (-1, 0, 3, 5), tol=0.3)
     assert len(out) == 4 and len(set(out)) == 1, out
+
+
+@pytest.mark.parametrize("tag", [1, 0x7ffffff0, 0x80000100, 0xffff0000])
+def test_tags_of_the_whole_range(exe, tag):
+    """Ghost refreshes of a launch late in the tags' range, over flags as a
+    cleared buffer holds them."""
+    out = lines(exe, (150, 8, 4), 40, 1000, 40, (-1, 0, 1), tag=tag) + lines(exe, (150, 8, 4), 40, 1000, 40, (-1,))
+    assert len(out) == 4 and len(set(out)) == 1, out
