@@ -318,8 +318,9 @@ enum { RES_RAN, RES_REFUSED, RES_LOST };
 // The solve after its set-up rebase, by resident launches (resident.hip).
 // how: RES_REFUSED if none could be launched (nothing has changed then);
 // RES_LOST if a block waited in vain, as when another process holds part of
-// the chip: ph + pd is then an iterate, taken cell by cell at the moment its
-// block gave up, and the sweeps go on from it.
+// the chip.  The last two intervals of the launch were then relaxed across
+// borders that may have been old: ph + pd is a start for the sweeps that is as
+// near the solution as they left it, and they repeat those two intervals.
 int run_resident(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve_stats* out, int& how) {
     const Geo& g = h->g;
     hipStream_t st = h->stream;
@@ -334,7 +335,7 @@ int run_resident(les_handle* h, const PBufs& P, double tol, int max_iter, les_so
         if (max_iter > 0) {
             const hipError_t e = timed(
                 h, KN_SOR, kNoTag,
-                [&] { return launch_resident(g, st, h->rplan, P, ctl, h->res_mem, h->prm.omega, K, R, iters, tag); }, 0);
+                [&] { return launch_resident(g, st, h->rplan, P, ctl, h->res_mem, h->prm.omega, K, R, iters, tag, h->res_spin); }, 0);
             if (e != hipSuccess && how == RES_REFUSED) {
                 (void)hipGetLastError();
                 h->resident = false;
@@ -345,7 +346,7 @@ int run_resident(les_handle* h, const PBufs& P, double tol, int max_iter, les_so
         how = RES_RAN;
         CK(hipMemcpyAsync(&hc, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
         CK(hipStreamSynchronize(st));
-        if (hc.pad_u[0]) {
+        if (hc.lost) {
             how = RES_LOST;
             h->resident = false;
             return LES_OK;
@@ -487,8 +488,13 @@ int run_solve(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve
         const int rc = run_resident(h, P, tol, max_iter, out, how);
         if (how == RES_RAN || rc != LES_OK) return rc;
         if (how == RES_LOST) {
-            c = (h->h_ctl->m + K - 1) / K;
-            CK(hipMemsetAsync(&ctl->done, 0, sizeof(int), st));
+            Ctl& hc = *h->h_ctl;
+            c = std::max(((long long)hc.m + K - 1) / K - 2, 0LL);
+            hc.m = (int)(c * K);
+            hc.done = 0;
+            hc.skip = 0;
+            hc.lost = 0;
+            CK(hipMemcpyAsync(ctl, &hc, sizeof(Ctl), hipMemcpyHostToDevice, st));
             CK(launch_fold(g, st, P, ctl));
             CK(launch_rebase(g, st, P, part, nullptr, nullptr, 0, ctl, 0));
         }
@@ -1319,7 +1325,7 @@ int les_autotune(les_handle* h, int32_t reps, int32_t* chosen, double* us_per_sw
             CK(launch_ctl_init(s, h->f.ctl, 1e-30, 1 << 30, n));
             CK(resident_take_tags(h, n, n, tag));
             CK(hipEventRecord(a, s));
-            if (launch_resident(g, s, h->rplan, h->S, h->f.ctl, h->res_mem, 1.0, n, 1 << 30, n, tag) != hipSuccess) {
+            if (launch_resident(g, s, h->rplan, h->S, h->f.ctl, h->res_mem, 1.0, n, 1 << 30, n, tag, h->res_spin) != hipSuccess) {
                 (void)hipGetLastError();
                 h->resident = false;
             }
@@ -1483,6 +1489,21 @@ int64_t les_bc_range(const les_grid* gr) {
     if (!gr || gr->nx < 1 || gr->ny < 1 || gr->nz < 1) return 0;
     const long long n = bc_items(gr->nx, gr->ny, gr->nz);
     return (int64_t)nblk(n) * kBlock;   // launch size, padded to whole blocks
+}
+
+// For tests, not part of the public ABI: whether the handle's solves take the
+// resident solver; spin >= -1 bounds its waits to that many polls (-1: the
+// launch is refused), next_tag > 0 clears its buffers and numbers on from there.
+int les_test_resident(les_handle* h, int32_t spin, uint32_t next_tag, int32_t* runs) {
+    if (!h || !runs) return LES_EINVAL;
+    if (spin >= -1) h->res_spin = spin;
+    if (next_tag && resident_runs(h) && resident_ready(h)) {
+        CK(launch_fill(h->stream, (float*)h->res_mem, (long long)(resident_bytes(h->rplan) / 4), 0.f));
+        CK(hipStreamSynchronize(h->stream));
+        h->res_tag = next_tag;
+    }
+    *runs = resident_runs(h) ? 1 : 0;
+    return LES_OK;
 }
 
 int les_bc_map(const les_grid* gr, int64_t item, int32_t* family, int32_t* a, int32_t* b) {

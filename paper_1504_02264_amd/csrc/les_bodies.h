@@ -395,7 +395,7 @@ __device__ __forceinline__ void ctl_init_body(Ctl* ctl, double tol, int max_iter
         ctl->resid = 0.0;
         ctl->reltmp2 = 0.0;
         ctl->skip = 0;
-        ctl->pad_u[0] = 0;
+        ctl->lost = 0;
     }
 }
 

@@ -133,7 +133,8 @@ struct Ctl {
     int K;              // check interval
     int max_iter;
     int skip;           // 1: the coming residual check is provably unsuccessful
-    unsigned pad_u[3];
+    unsigned lost;      // a block of the resident solver waited in vain
+    unsigned pad_u[2];
     double tol;
     double rhs2;        // sum rhs^2 (after mean removal)
     double rhs_sum;     // sum rhs (singular case)
@@ -197,6 +198,7 @@ struct SolveGraph {
 };
 // Decomposition of a grid for the resident solver (resident.hip): shape -1 if
 // the grid does not fit the chip's registers.
+constexpr int kResSpin = 1 << 21;   // polls of one wait of its blocks: more than a second
 struct ResPlan {
     int shape;
     int nbx, nby, nbz;   // tiles per axis
@@ -250,6 +252,7 @@ struct les_handle {
     les::ResPlan rplan{};
     void* res_mem = nullptr;
     uint32_t res_tag = 1;
+    int res_spin = les::kResSpin;   // polls of one wait (negative: no launch, for tests)
     // twinned double-buffer comparison solver (twinned.hip): pairs, partials
     void* tw_q = nullptr;
     double* tw_part = nullptr;
@@ -387,7 +390,7 @@ ResPlan resident_plan(const Geo& g, int cus);
 size_t resident_bytes(const ResPlan& p);
 unsigned resident_tags(int iters, int K);
 hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const PBufs& P, Ctl* ctl, void* mem,
-                           double omega, int K, int R, int iters, unsigned tag);
+                           double omega, int K, int R, int iters, unsigned tag, int spin);
 hipError_t launch_project(const Geo& g, hipStream_t st, float* us, float* vs, float* ws,
                           const PBufs& P);
 hipError_t launch_bc(const Geo& g, hipStream_t st, float* u, float* v, float* w);

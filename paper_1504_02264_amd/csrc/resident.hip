@@ -39,9 +39,12 @@
 // border cells follow and are published at once.
 //
 // All blocks of a launch wait for each other, so they are launched
-// cooperatively (resident together or not at all); every wait is bounded, and
-// a block that waits in vain raises ctl->pad_u[0] and leaves (the host then
-// goes on with sweep launches).
+// cooperatively (resident together or not at all); every wait is bounded.  A
+// wavefront that waits in vain goes on without waiting to the end of its check
+// interval, on borders that may be old and publishing what it makes of them;
+// there its block raises ctl->lost, stores its cells and leaves.  Blocks that
+// wait for it follow within their next interval, so all but the last two
+// intervals of a lost launch are sound (the host goes on with sweep launches).
 #include "les_bodies.h"
 
 namespace les {
@@ -52,7 +55,6 @@ constexpr int kResWaves = 8;
 constexpr int kResThreads = 64 * kResWaves;
 constexpr int kResSlots = 4;          // publications kept: a slot is rewritten four tags later
 constexpr int kResPad = 16;           // flags 64 bytes apart
-constexpr int kResSpin = 1 << 21;     // polls of one wait (more than a second)
 
 struct ResArgs {
     Geo g;
@@ -66,6 +68,7 @@ struct ResArgs {
     float omega;
     double omega_d;
     int K, R, cap;
+    int spin;        // polls of one wait
     unsigned tag0;
 };
 
@@ -346,7 +349,7 @@ struct Resident {
             bool ok = true;
             if (see) ok = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - n <= 1u;
             if (__builtin_expect(dead || __all(ok), 1)) break;
-            if (spin >= kResSpin) dead = true;
+            if (spin >= a.spin) dead = true;
         }
         asm volatile("" ::: "memory");   // nothing that follows comes before the flags
     }
@@ -380,7 +383,7 @@ struct Resident {
                         for (int r = 0; r < RY; ++r) ok = ok && (unsigned)(vz[r] >> 32) == tag;
                 }
                 if (__builtin_expect(dead || __all(ok), 1)) break;
-                if (spin >= kResSpin) dead = true;
+                if (spin >= a.spin) dead = true;
             }
         }
         auto& h = sm.halo[tag & (Smem::kSets - 1)][wv];
@@ -678,7 +681,7 @@ struct Resident {
                         ok = ok && (unsigned)(v[q] >> 32) == gtag;
                     }
                 if (__builtin_expect(dead || __all(ok), 1)) break;
-                if (spin >= kResSpin) dead = true;
+                if (spin >= a.spin) dead = true;
             }
             if (need)
 #pragma unroll
@@ -720,7 +723,7 @@ __global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(2, 
     double R = ctl->resid, reltmp2 = 0.0;
     unsigned gtag = a.tag0;
     auto finish = [&](bool lost) {
-        if (lost && threadIdx.x == 0) ctl->pad_u[0] = 1;
+        if (lost && threadIdx.x == 0) ctl->lost = 1;
         if (w.t != 0 || threadIdx.x != 0) return;
         ctl->m = m;
         ctl->skip = 0;
@@ -855,7 +858,8 @@ size_t resident_bytes(const ResPlan& p) {
 // most three sums and one publication per check interval
 unsigned resident_tags(int iters, int K) { return 2u * (unsigned)iters + 4u * (unsigned)(iters / K + 2) + 8u; }
 
-hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const PBufs& P, Ctl* ctl, void* mem, double omega, int K, int R, int iters, unsigned tag) {
+hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const PBufs& P, Ctl* ctl, void* mem, double omega, int K, int R, int iters, unsigned tag, int spin) {
+    if (spin < 0) return hipErrorInvalidValue;
     ResArgs a{};
     a.g = g;
     a.P = P;
@@ -873,6 +877,7 @@ hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const
     a.K = K;
     a.R = R;
     a.cap = iters;
+    a.spin = spin;
     a.tag0 = tag;
     return kShapes[p.shape].start(a, p.blocks, st);
 }

@@ -6,10 +6,11 @@
 // it moves by one collective operation only when all others wait.  What the
 // kernel computes must not depend on it.
 //
-//   resident_host nx ny nz K R max_iter tag0 tol victim...
+//   resident_host nx ny nz K R max_iter tag0 tol spin victim...
 //
-// victim -1: blocks run in turn.  Prints, for each victim, a line with the
-// control block and checksums of ph, pd and r0 of both colours.
+// victim -1: blocks run in turn; spin: polls of one wait (0: the kernel's own
+// bound).  Prints, for each victim, a line with the control block and checksums
+// of ph, pd and r0 of both colours.
 #include <hip/hip_runtime.h>
 #include <ucontext.h>
 
@@ -274,7 +275,7 @@ extern "C" hipError_t hipLaunchCooperativeKernel(const void* f, dim3 blocks, dim
 }
 
 int main(int argc, char** argv) {
-    if (argc < 10) return 2;
+    if (argc < 11) return 2;
     auto num = [&](int q) { return std::atoll(argv[q]); };
     les::Geo g{};
     g.nx = (int)num(1);
@@ -294,7 +295,7 @@ int main(int argc, char** argv) {
     g.outflow = 1;
     const les::ResPlan p = les::resident_plan(g, 256);
     if (p.shape < 0) return 4;
-    for (int arg = 9; arg < argc; ++arg) {
+    for (int arg = 10; arg < argc; ++arg) {
         host::g_victim = (int)num(arg);
         std::vector<float> mem[8];
         for (auto& v : mem) v.assign(g.ctot, 0.f);
@@ -326,8 +327,8 @@ int main(int argc, char** argv) {
         ctl.tol = std::atof(argv[8]);
         ctl.rhs2 = rhs2;
         std::vector<unsigned long long> x(les::resident_bytes(p) / 8 + 1, 0);
-        les::launch_resident(g, nullptr, p, P, &ctl, x.data(), 1.8, K, R, max_iter, (unsigned)num(7));
-        std::printf("blocks %u ghosts %d m %d done %d lost %u resid %.17g", p.blocks, p.g, ctl.m, ctl.done, ctl.pad_u[0], ctl.resid);
+        les::launch_resident(g, nullptr, p, P, &ctl, x.data(), 1.8, K, R, max_iter, (unsigned)num(7), num(9) ? (int)num(9) : les::kResSpin);
+        std::printf("blocks %u ghosts %d m %d done %d lost %u resid %.17g", p.blocks, p.g, ctl.m, ctl.done, ctl.lost, ctl.resid);
         for (int q = 0; q < 6; ++q) {
             unsigned long long h = 1469598103934665603ull;
             for (float v : mem[q]) {
@@ -337,7 +338,10 @@ int main(int argc, char** argv) {
             }
             std::printf(" %016llx", h);
         }
-        std::printf("\n");
+        bool finite = true;
+        for (int q = 0; q < 6; ++q)
+            for (float v : mem[q]) finite = finite && isfinite(v);
+        std::printf(" finite %d\n", finite);
         std::fflush(stdout);
     }
     return 0;

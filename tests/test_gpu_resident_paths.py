@@ -1,0 +1,134 @@
+"""The resident solver where it is hard to see whether it ran: the tests ask the
+handle whether its solves take it, and the timing counters, which count every
+iteration of a resident solve and one check interval in eight of the sweeps.
+Rows split between tiles over the depths of the ghost columns and the check
+intervals around them; tags that run out; launches that are refused and blocks
+that wait in vain, after which the sweeps go on."""
+import ctypes as C
+
+import numpy as np
+import pytest
+
+import oracle
+import paper_1504_02264_amd as les
+from les_inputs import random_rhs
+
+from test_gpu_resident import same
+
+pytestmark = pytest.mark.gpu
+
+SPIN = 1 << 21   # the solver's own bound of a wait
+SPACING = (2.0, 3.0, 1.5)
+
+
+def resident(g, spin=-2, tag=0):
+    f = les.lib().les_test_resident
+    f.argtypes = [C.c_void_p, C.c_int32, C.c_uint32, C.POINTER(C.c_int32)]
+    runs = C.c_int32()
+    assert f(g.h, spin, tag, C.byref(runs)) == les.LES_OK
+    return runs.value
+
+
+def inputs(shape):
+    nx, ny, nz = shape
+    return random_rhs(nx, ny, nz, seed=nx + 7 * ny + 31 * nz, smooth=1), random_rhs(nx, ny, nz, seed=5)
+
+
+def make(shape, variant=None, **kw):
+    g = les.LES(*shape, *SPACING, 0.05, **kw)
+    if variant is not None:
+        g.set_sor_variant(variant)
+    assert resident(g) == (variant is None)
+    return g
+
+
+@pytest.mark.parametrize("nx,depth", [(223, 4), (224, 4), (150, 13), (451, 9)])
+@pytest.mark.parametrize("K,R", [(1, 1), (3, 1), (4, 32), (8, 16), (0, 1), (1000, 1), (64, 2)])
+def test_ghost_columns_equal_sweep_launches(nx, depth, K, R):
+    """The depth itself for K = 0; intervals below, at and above it, folds in
+    every interval and in few."""
+    shape = (nx, 17, 9)
+    K = K or depth
+    rhs, p0 = inputs(shape)
+    print(f"[ghosts] nx={nx} K={K} R={R}", flush=True)
+    for n in (4 * depth + 3, 700):
+        out = []
+        for variant in (None, 1):
+            g = make(shape, variant, check_every=K, rebase_every=R, timing=1)
+            try:
+                out.append(g.pressure_solve(rhs, p0, tol=1e-9, max_iter=n))
+                if variant is None:
+                    assert resident(g) and g.get_timing()["sor"][1] == out[0][1]["iters"] == n
+            finally:
+                g.close()
+        same(*out)
+
+
+@pytest.mark.parametrize("shape", [(150, 33, 11), (70, 131, 67), (300, 300, 90)])
+def test_tags_run_out(shape):
+    """Launches before, across and after the end of the tags' range."""
+    rhs, p0 = inputs(shape)
+    g, ref = make(shape, check_every=64, rebase_every=2), make(shape, 1, check_every=64, rebase_every=2)
+    try:
+        want = ref.pressure_solve(rhs, p0, tol=1e-9, max_iter=130)
+        for tag in (0x7fffffff - 400, 0xffffffff - 800):
+            assert resident(g, tag=tag)
+            for _ in range(4):
+                same(g.pressure_solve(rhs, p0, tol=1e-9, max_iter=130), want)
+        assert resident(g)
+    finally:
+        g.close()
+        ref.close()
+
+
+def residual(rhs, p, shape):
+    """The oracle's relative residual of p, and how far the solver's, whose p is a
+    float32 value and an exact rest, can be from it: the rest is at most 2^-24 |p|,
+    so 2^-24 || |A| |p| || / ||rhs||, and |A| |p| = A |p| + 2 diag |p| with A's
+    diagonal at most 3 / dx^2 + 2 / dy^2 + 2 / dz^2."""
+    o = oracle.Oracle(*shape, *SPACING, 0.05)
+    dx, dy, dz = SPACING
+    diag = 3 / dx ** 2 + 2 / dy ** 2 + 2 / dz ** 2
+    q = np.abs(p.astype(np.float64))
+    slack = np.linalg.norm(o.apply_A(q) + 2 * diag * q) / np.linalg.norm(rhs.astype(np.float64))
+    return o.residual(rhs, p), 2.0 ** -24 * slack
+
+
+@pytest.mark.parametrize("shape", [(64, 33, 11), (150, 33, 11), (70, 131, 67)])
+@pytest.mark.parametrize("K,max_iter", [(4, 20000), (4, 7), (4, 100), (64, 640), (20, 9)])
+def test_solve_goes_on_after_a_lost_launch(shape, K, max_iter):
+    rhs, p0 = inputs(shape)
+    g = make(shape, check_every=K, rebase_every=max(1, 128 // K), timing=1)
+    ref = make(shape, 1, check_every=K, rebase_every=max(1, 128 // K))
+    try:
+        resident(g, spin=0)
+        print(f"[lost] {shape} K={K} max_iter={max_iter}", flush=True)
+        p, st, rc = g.pressure_solve(rhs, p0, tol=1e-5, max_iter=max_iter)
+        assert not resident(g)
+        r, slack = residual(rhs, p, shape)
+        assert abs(r - st["resid"]) <= slack
+        # stops as the sweeps do (150 columns take more than 20000 iterations)
+        want = ref.pressure_solve(rhs, p0, tol=1e-5, max_iter=max_iter)
+        print(f"[lost] sweeps: {want[1]} here: {st}", flush=True)
+        assert rc == want[2] and st["converged"] == (st["resid"] <= 1e-5)
+        assert st["converged"] or st["iters"] == max_iter
+        # and the handle goes on, with its sweep launches
+        resident(g, spin=SPIN)
+        same(g.pressure_solve(rhs, p0, tol=1e-5, max_iter=300), ref.pressure_solve(rhs, p0, tol=1e-5, max_iter=300))
+        assert not resident(g)
+    finally:
+        g.close()
+        ref.close()
+
+
+def test_refused_launch():
+    shape = (150, 33, 11)
+    rhs, p0 = inputs(shape)
+    g, ref = make(shape), make(shape, 0)
+    try:
+        resident(g, spin=-1)
+        same(g.pressure_solve(rhs, p0, max_iter=300), ref.pressure_solve(rhs, p0, max_iter=300))
+        assert not resident(g, spin=SPIN)
+    finally:
+        g.close()
+        ref.close()

@@ -23,8 +23,8 @@ def exe(tmp_path_factory):
     return out
 
 
-def lines(exe, shape, K, R, max_iter, victims, tag=1, tol=1e-12):
-    r = subprocess.run([exe] + [str(v) for v in (*shape, K, R, max_iter, tag, tol, *victims)], capture_output=True, text=True,
+def lines(exe, shape, K, R, max_iter, victims, tag=1, tol=1e-12, spin=0):
+    r = subprocess.run([exe] + [str(v) for v in (*shape, K, R, max_iter, tag, tol, spin, *victims)], capture_output=True, text=True,
                        timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
     return r.stdout.splitlines()
@@ -45,7 +45,7 @@ def test_order_of_tiles_in_a_row(exe, shape, K, R, max_iter, tol):
 
 
 def test_order_of_tiles_in_rows_and_planes(exe):
-    out = lines(exe, (30, 9, 9), 4, 32, 12, (-1, 0, 3, 5), tol=0.3)
+    out = lines(exe, (30, 17, 9), 4, 32, 12, (-1, 0, 4, 8), tol=0.2)
     assert len(out) == 4 and len(set(out)) == 1, out
 
 
@@ -55,3 +55,13 @@ def test_tags_of_the_whole_range(exe, tag):
     cleared buffer holds them."""
     out = lines(exe, (150, 8, 4), 40, 1000, 40, (-1, 0, 1), tag=tag) + lines(exe, (150, 8, 4), 40, 1000, 40, (-1,))
     assert len(out) == 4 and len(set(out)) == 1, out
+
+
+@pytest.mark.parametrize("shape", [(150, 8, 4), (30, 17, 4)])
+@pytest.mark.parametrize("K,R", [(4, 32), (20, 1)])
+def test_waits_in_vain(exe, shape, K, R):
+    """A wait that gives up after two polls: every block leaves all the same, the
+    launch says that it was lost, and what it leaves is finite."""
+    for out in lines(exe, shape, K, R, 40, (-1, 0, 1), spin=1):
+        assert " lost 1 " in out and out.endswith("finite 1"), out
+        assert 0 < int(out.split(" m ")[1].split()[0]) <= 40, out
