@@ -359,13 +359,21 @@ int les_get_timing(les_handle* h, les_timing* out, int32_t reset);
  *
  * Uniform grids whose pressure system fits the chip's registers and LDS (up
  * to about 10 million cells) are solved by a resident kernel instead, one
- * cooperative launch for thousands of iterations, with the same arithmetic
- * and the same results bit for bit; sweep launches serve the other grids,
- * ensembles and the allocation-free solve.  les_set_sor_variant turns it off
- * for the handle (its solves then use the variant asked for), les_autotune
- * turns it on where it is faster than every variant.  Its face buffers (tens
- * of MB at most) are allocated at the handle's first solve; without the
- * memory for them the handle uses its sweep variant.
+ * launch for thousands of iterations, with the same arithmetic and the same
+ * results bit for bit; sweep launches serve the other grids, ensembles and
+ * the allocation-free solve.  les_set_sor_variant turns it off for the
+ * handle (its solves then use the variant asked for), les_autotune turns it
+ * on where it is faster than every variant.  Its face buffers (tens of MB at
+ * most) are allocated at the handle's first solve; without the memory for
+ * them the handle uses its sweep variant.  A launch needs compute units for
+ * itself (one for a block of 128 x 8 x 4 cells to one of 128 x 24 x 16, as
+ * the grid asks): solves of several threads of a process run side by side
+ * while they all fit and in turn otherwise, and one that waits longer than
+ * 0.2 s takes its sweep launches until there is room.  Processes that share
+ * a device do not know of each other: a launch that finds part of the chip
+ * taken by another's gives up after a second or more, and the handle keeps
+ * to its sweep launches from then on (les_autotune turns the resident
+ * kernel on again).
  *
  * Autotuner: times every variant for reps back-to-back pairs of launches
  * on this handle's grid, keeps the fastest for all later solves of the

@@ -1273,6 +1273,11 @@ int les_ensemble_step(les_ensemble* e, int32_t nsteps, les_ensemble_stats* st, i
         }
         e->graphs_ready = true;
     }
+    // the persistent solve's blocks wait for each other on the whole chip, so it
+    // keeps apart from resident solves of other threads (whose waits are bounded:
+    // it goes on in any case)
+    ChipShare share(e->members[0]->device, e->members[0]->cus);
+    if (e->mode == LES_ENSEMBLE_PERSISTENT) (void)share.take(e->members[0]->cus, 1000);
     for (int s = 0; s < nsteps; ++s) {
         ECK(hipGraphLaunch(e->pre[s & 1], e->stream));
         int rc = launch_solve(e, e->stream);

@@ -7,15 +7,60 @@
 // waits for the host between SOR iterations.
 #include <algorithm>
 #include <chrono>
+#include <climits>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
 #include "les_impl.h"
 
 using namespace les;
+
+namespace les {
+namespace {
+struct Chip {
+    std::mutex m;
+    std::condition_variable cv;
+    long long held = 0;
+    ChipShare* first = nullptr;   // waiting, in the order they came
+};
+constexpr int kDevices = 64;
+Chip g_chips[kDevices];
+}  // namespace
+
+bool ChipShare::take(long long units, int ms) {
+    if (device_ < 0 || device_ >= kDevices) return false;
+    Chip& c = g_chips[device_];
+    std::unique_lock<std::mutex> l(c.m);
+    ChipShare** at = &c.first;
+    while (*at) at = &(*at)->next_;
+    *at = this;
+    next_ = nullptr;
+    const bool ok = c.cv.wait_for(l, std::chrono::milliseconds(ms),
+                                  [&] { return c.first == this && c.held + units <= cus_; });
+    for (at = &c.first; *at != this; at = &(*at)->next_) {}
+    *at = next_;
+    if (ok) c.held += held_ = units;
+    l.unlock();
+    c.cv.notify_all();   // the next in the queue
+    return ok;
+}
+
+void ChipShare::give() {
+    if (!held_) return;
+    Chip& c = g_chips[device_];
+    {
+        std::lock_guard<std::mutex> l(c.m);
+        c.held -= held_;
+    }
+    held_ = 0;
+    c.cv.notify_all();
+}
+}  // namespace les
 
 namespace {
 
@@ -313,58 +358,54 @@ hipError_t resident_take_tags(les_handle* h, int iters, int K, unsigned& tag) {
     return hipSuccess;
 }
 
-enum { RES_RAN, RES_REFUSED, RES_LOST };
+// A solve waits at most this long for room on the chip (longer than a launch of
+// kResidentIters iterations runs) before it takes its sweep launches.
+constexpr int kResidentPatienceMs = 200;
 
-// The solve after its set-up rebase, by resident launches (resident.hip).
-// how: RES_REFUSED if none could be launched (nothing has changed then);
-// RES_LOST if a block waited in vain, as when another process holds part of
-// the chip.  The last two intervals of the launch were then relaxed across
-// borders that may have been old: ph + pd is a start for the sweeps that is as
-// near the solution as they left it, and they repeat those two intervals.
-int run_resident(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve_stats* out, int& how) {
-    const Geo& g = h->g;
+enum { RES_DONE, RES_BUSY, RES_REFUSED, RES_LOST };
+
+// The solve from check interval c + 1 on by resident launches (resident.hip),
+// behind the work on the stream; c and own (resident iterations) are advanced.
+// RES_BUSY: no room on the chip within `patience` ms, and RES_REFUSED: nothing
+// could be launched; the sweeps go on from interval c + 1.
+// RES_LOST: a block waited in vain, as when another process holds part of the
+// chip.  The last two intervals of the launch were then relaxed across borders
+// that may have been old: ph + pd is a start for the sweeps that is as near the
+// solution as they left it, and they repeat those two intervals.
+int run_resident(les_handle* h, const PBufs& P, int max_iter, int patience, long long& c, long long& own, int& how) {
     hipStream_t st = h->stream;
-    Ctl* ctl = h->f.ctl;
     const int K = h->prm.check_every, R = h->prm.rebase_every;
-    how = RES_REFUSED;
     const int iters = std::min(max_iter, std::max(kResidentIters / K, 1) * K);
     Ctl& hc = *h->h_ctl;
+    ChipShare share(h->device, h->cus);
     do {
-        unsigned tag = 0;
-        CK(resident_take_tags(h, iters, K, tag));
-        if (max_iter > 0) {
-            const hipError_t e = timed(
-                h, KN_SOR, kNoTag,
-                [&] { return launch_resident(g, st, h->rplan, P, ctl, h->res_mem, h->prm.omega, K, R, iters, tag, h->res_spin); }, 0);
-            if (e != hipSuccess && how == RES_REFUSED) {
-                (void)hipGetLastError();
-                h->resident = false;
-                return LES_OK;
-            }
-            CK(e);
-        }
-        how = RES_RAN;
-        CK(hipMemcpyAsync(&hc, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
-        CK(hipStreamSynchronize(st));
-        if (hc.lost) {
-            how = RES_LOST;
-            h->resident = false;
+        if (!share.take(h->rplan.blocks, patience)) {
+            how = RES_BUSY;
             return LES_OK;
         }
-    } while (!hc.done && max_iter > 0);
-    if (h->prm.timing) {   // every iteration is timed, none sampled
-        tresolve(h, kNoTag);
-        h->tcount[KN_SOR] += hc.m;
-    }
-    if (out) {
-        out->iters = hc.m;
-        out->resid = hc.resid;
-        out->rhs_norm = std::sqrt(hc.rhs2);
-        out->reltmp2 = hc.reltmp2;
-        out->converged = (hc.done == 1 || (hc.done == 0 && hc.resid <= tol)) ? 1 : 0;
-    }
-    if (hc.done == 3 || !std::isfinite(hc.rhs2)) return set_err(h, LES_ENONFINITE, "non-finite residual norm");
-    if (hc.done == 2 || (hc.done == 0 && !(hc.resid <= tol))) return LES_NOT_CONVERGED;
+        unsigned tag = 0;
+        CK(resident_take_tags(h, iters, K, tag));
+        const hipError_t e = timed(
+            h, KN_SOR, kNoTag,
+            [&] { return launch_resident(h->g, st, h->rplan, P, h->f.ctl, h->res_mem, h->prm.omega, K, R, iters, tag, h->res_spin); }, 0);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            h->resident = false;
+            how = RES_REFUSED;
+            return LES_OK;
+        }
+        CK(hipMemcpyAsync(&hc, h->f.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+        CK(hipStreamSynchronize(st));
+        share.give();
+        if (hc.lost) {
+            h->resident = false;
+            how = RES_LOST;
+            return LES_OK;
+        }
+        own += std::max(hc.m - c * K, 0LL);
+        c = std::max(c, ((long long)hc.m + K - 1) / K);
+    } while (!hc.done);
+    how = RES_DONE;
     return LES_OK;
 }
 
@@ -483,22 +524,6 @@ int run_solve(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve
     long long c = 0;
     CK(launch_fold(g, st, P, ctl));
     CK(tm(KN_REBASE, 0, [&] { return launch_rebase(g, st, P, part, nullptr, nullptr, 0, ctl, 0); }));
-    if (!direct && resident_runs(h) && resident_ready(h)) {
-        int how = RES_RAN;
-        const int rc = run_resident(h, P, tol, max_iter, out, how);
-        if (how == RES_RAN || rc != LES_OK) return rc;
-        if (how == RES_LOST) {
-            Ctl& hc = *h->h_ctl;
-            c = std::max(((long long)hc.m + K - 1) / K - 2, 0LL);
-            hc.m = (int)(c * K);
-            hc.done = 0;
-            hc.skip = 0;
-            hc.lost = 0;
-            CK(hipMemcpyAsync(ctl, &hc, sizeof(Ctl), hipMemcpyHostToDevice, st));
-            CK(launch_fold(g, st, P, ctl));
-            CK(launch_rebase(g, st, P, part, nullptr, nullptr, 0, ctl, 0));
-        }
-    }
     const long long n_checks = max_iter > 0 ? ((long long)max_iter + K - 1) / K : 0;
     // batches of 2, 2, 4 intervals (a solve that converges at once is
     // noticed early), then 8, 16, 32, 64 (capped below): from interval 8 on
@@ -512,7 +537,31 @@ int run_solve(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve
     int bi = 0;
     int slot = 0;
     bool pending = false;
+    bool resident = !direct && n_checks > 0 && resident_runs(h) && resident_ready(h);
+    int patience = kResidentPatienceMs;
+    long long own = 0;   // resident iterations
     while (c < n_checks) {
+        if (resident) {
+            int how = RES_DONE;
+            const int rc = run_resident(h, P, max_iter, patience, c, own, how);
+            if (rc != LES_OK) return rc;
+            if (how == RES_DONE) break;
+            resident = how == RES_BUSY;
+            patience = 0;
+            if (how == RES_LOST) {
+                Ctl& hc = *h->h_ctl;
+                c = std::max(((long long)hc.m + K - 1) / K - 2, 0LL);
+                hc.m = (int)(c * K);
+                hc.done = 0;
+                hc.skip = 0;
+                hc.lost = 0;
+                CK(hipMemcpyAsync(ctl, &hc, sizeof(Ctl), hipMemcpyHostToDevice, st));
+                CK(launch_fold(g, st, P, ctl));
+                CK(launch_rebase(g, st, P, part, nullptr, nullptr, 0, ctl, 0));
+                pending = false;
+                bi = 0;
+            }
+        }
         const long long nb = std::min<long long>(std::min(kBatches[bi], batch_cap), n_checks - c);
         long long q = 0;
         while (q < nb) {
@@ -540,8 +589,15 @@ int run_solve(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve
     CK(hipMemcpyAsync(h->h_ctl, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
     CK(hipStreamSynchronize(st));
     const Ctl& hc = *h->h_ctl;
-    // the check that stopped the solve is interval ceil(m / K)
-    if (timing) tresolve(h, ((long long)hc.m + K - 1) / K);
+    if (timing) {
+        // every resident iteration is timed: sampled sweep launches beside them
+        // (other units) are left out, as is a resident launch that did none
+        for (auto& b : h->tpending)
+            if (b.kind == KN_SOR && (b.tag != kNoTag) == (own > 0)) b.tag = LLONG_MAX;
+        // the check that stopped the solve is interval ceil(m / K)
+        tresolve(h, ((long long)hc.m + K - 1) / K);
+        h->tcount[KN_SOR] += own;
+    }
     if (out) {
         out->iters = hc.m;
         out->resid = hc.resid;
@@ -811,12 +867,9 @@ int create_impl(const les_grid* gr, const les_spacing* s, const double* const* w
     h->prof.assign((size_t)g.nz, 0.f);
     h->prof1.assign((size_t)g.nz, 0.f);
     h->sor_variant = sor_default_variant(g);
-    int coop = 0, cus = 0;
-    if (hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, h->device) == hipSuccess && coop &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, h->device) == hipSuccess) {
-        h->rplan = resident_plan(g, cus);
-        h->resident = h->rplan.shape >= 0;
-    }
+    if (hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device) != hipSuccess) h->cus = 0;
+    h->rplan = resident_plan(g, h->cus);
+    h->resident = h->rplan.shape >= 0;
     *out = h;
     return LES_OK;
 }
@@ -1317,7 +1370,8 @@ int les_autotune(les_handle* h, int32_t reps, int32_t* chosen, double* us_per_sw
     // the resident solver on the same zero system: one interval of reps
     // iterations and its check per launch (it stops there, the norm being 0)
     h->resident = h->rplan.shape >= 0;
-    if (resident_runs(h) && resident_ready(h)) {
+    ChipShare share(h->device, h->cus);
+    if (resident_runs(h) && resident_ready(h) && share.take(h->rplan.blocks, kResidentPatienceMs)) {
         const int n = std::max(8 * reps, 128);
         float ms = 0.f;
         for (int r = 0; r < 2 && h->resident; ++r) {   // the first launch loads the code

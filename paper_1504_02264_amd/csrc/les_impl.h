@@ -249,6 +249,7 @@ struct les_handle {
     uint64_t sgraph_tick = 0;
     // resident solver: whether solves take it, its plan, face buffers and next tag
     bool resident = false;
+    int cus = 0;                    // compute units of the device
     les::ResPlan rplan{};
     void* res_mem = nullptr;
     uint32_t res_tag = 1;
@@ -384,6 +385,25 @@ hipError_t launch_sor_rb(const Geo& g, hipStream_t st, const PBufs& P, int parit
 // buffers as launch_sor_rb
 hipError_t launch_sor_rb2(const Geo& g, hipStream_t st, const PBufs& P, int parity, float omega,
                           int local_iter, double* rel0, double* rel1, const Ctl* ctl, int variant);
+// Compute units of a device for a kernel whose blocks wait for each other.  Such
+// kernels finish if all their blocks are on the chip together, a block per unit;
+// two that are dispatched at once could each hold units that the other needs.
+// So a thread takes units for all blocks of its launch and gives them back when
+// the launch has ended; units are served in the order of the requests.
+class ChipShare {
+public:
+    ChipShare(int device, int cus) : device_(device), cus_(cus) {}
+    ~ChipShare() { give(); }
+    ChipShare(const ChipShare&) = delete;
+    ChipShare& operator=(const ChipShare&) = delete;
+    bool take(long long units, int ms);   // waits at most ms for them
+    void give();
+
+private:
+    int device_, cus_;
+    long long held_ = 0;
+    ChipShare* next_ = nullptr;
+};
 // resident solver (resident.hip): up to `iters` more iterations of the solve
 // ctl describes (stopping tests included), the face buffers in mem
 ResPlan resident_plan(const Geo& g, int cus);

@@ -258,7 +258,7 @@ struct __amdgpu_buffer_rsrc_t {};
 #include RESIDENT_SOURCE
 
 #undef volatile
-extern "C" hipError_t hipLaunchCooperativeKernel(const void* f, dim3 blocks, dim3 threads, void** args, unsigned, hipStream_t) {
+extern "C" hipError_t hipLaunchKernel(const void* f, dim3 blocks, dim3 threads, void** args, size_t, hipStream_t) {
     host::Grid grid;
     grid.n = blocks.x;
     grid.victim = host::g_victim;

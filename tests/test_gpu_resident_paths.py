@@ -5,13 +5,14 @@ Rows split between tiles over the depths of the ghost columns and the check
 intervals around them; tags that run out; launches that are refused and blocks
 that wait in vain, after which the sweeps go on."""
 import ctypes as C
+import threading
 
 import numpy as np
 import pytest
 
 import oracle
 import paper_1504_02264_amd as les
-from les_inputs import random_rhs
+from les_inputs import log_law_profile, random_rhs
 
 from test_gpu_resident import same
 
@@ -132,3 +133,79 @@ def test_refused_launch():
     finally:
         g.close()
         ref.close()
+
+
+@pytest.mark.parametrize("shape,n", [((33, 17, 9), 20000), ((150, 33, 11), 700), ((128, 128, 64), 400)])
+def test_solves_in_several_threads(shape, n):
+    """Solves side by side, on a part of the chip each or in turn: each gives what
+    it gives alone."""
+    def run(g, seed, out):
+        rhs, p0 = random_rhs(*shape, seed=seed, smooth=1), random_rhs(*shape, seed=5 + seed)
+        for q in range(4):
+            out[seed, q] = g.pressure_solve(rhs, p0, tol=1e-5, max_iter=n)
+
+    handles = [make(shape) for _ in range(4)]
+    try:
+        alone, beside = {}, {}
+        for q, g in enumerate(handles):
+            run(g, q, alone)
+        threads = [threading.Thread(target=run, args=(g, q, beside)) for q, g in enumerate(handles)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        assert len(alone) == len(beside) == 16
+        for k in alone:
+            same(alone[k], beside[k])
+        assert all(resident(g) for g in handles)
+    finally:
+        for g in handles:
+            g.close()
+
+
+def test_solves_beside_a_persistent_ensemble():
+    """Both kinds of launch whose blocks wait for each other, from two threads."""
+    prof = log_law_profile(18, 2.0)
+
+    def members():
+        out = []
+        for q in range(2):
+            g = les.LES(40 + 8 * q, 32, 18, 4.0, 4.0, 2.0, 0.05, None, max_iter=400)
+            g.set_inflow(prof, 0.01, q)
+            out.append(g)
+        e = les.Ensemble(out)
+        e.set_mode(les.ENSEMBLE_PERSISTENT)
+        return e, out
+
+    def steps(e, ms, out):
+        for _ in range(8):
+            e.step(1)
+        out.extend(m.get_fields() for m in ms)
+
+    def solves(g, out):
+        rhs, p0 = inputs((64, 64, 32))
+        for _ in range(12):
+            out.append(g.pressure_solve(rhs, p0, tol=1e-9, max_iter=300))
+
+    (ea, a), (eb, b) = members(), members()
+    gs = [make((64, 64, 32)) for _ in range(2)]
+    try:
+        want, got, one, two = [], [], [], []
+        steps(ea, a, want)
+        threads = [threading.Thread(target=steps, args=(eb, b, got)), threading.Thread(target=solves, args=(gs[0], one))]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        solves(gs[1], two)
+        for x, y in zip(want, got):
+            assert all(np.array_equal(f, h) for f, h in zip(x, y))
+        assert len(one) == len(two) == 12
+        for x, y in zip(one, two):
+            same(x, y)
+        assert resident(gs[0]) and resident(gs[1])
+    finally:
+        ea.close()
+        eb.close()
+        for g in a + b + gs:
+            g.close()
