@@ -370,10 +370,11 @@ int les_get_timing(les_handle* h, les_timing* out, int32_t reset);
  * the grid asks): solves of several threads of a process run side by side
  * while they all fit and in turn otherwise, and one that waits longer than
  * 0.2 s takes its sweep launches until there is room.  Processes that share
- * a device do not know of each other: a launch that finds part of the chip
- * taken by another's gives up after a second or more, and the handle keeps
- * to its sweep launches from then on (les_autotune turns the resident
- * kernel on again).
+ * a device do not know of each other: a launch that does not get its units
+ * within some milliseconds ends again, the solve takes its sweep launches, and
+ * the handle tries anew after 1, 3, 7 .. 63 solves.  A launch whose blocks lose
+ * each other all the same (a queue suspended for more than a second) leaves
+ * the handle to its sweep launches until les_autotune.
  *
  * Autotuner: times every variant for reps back-to-back pairs of launches
  * on this handle's grid, keeps the fastest for all later solves of the

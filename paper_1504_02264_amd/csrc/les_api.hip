@@ -330,14 +330,18 @@ constexpr int kResidentIters = 8192, kResidentMaxK = 32768;
 
 bool resident_runs(const les_handle* h) { return h->resident && h->prm.check_every <= kResidentMaxK; }
 
+// Clears the resident solver's buffers; tags go on from `tag`.
+hipError_t resident_clear(les_handle* h, unsigned tag) {
+    h->res_tag = tag;
+    h->res_launches = 0;
+    return launch_fill(h->stream, (float*)h->res_mem, (long long)(resident_bytes(h->rplan) / 4), 0.f);
+}
+
 // Face buffers of the resident solver; without the memory for them the handle
 // goes on with sweep launches.
 bool resident_ready(les_handle* h) {
     if (h->res_mem) return true;
-    const size_t bytes = resident_bytes(h->rplan);
-    if (hipMalloc(&h->res_mem, bytes) == hipSuccess &&
-        launch_fill(h->stream, (float*)h->res_mem, (long long)(bytes / 4), 0.f) == hipSuccess)
-        return true;
+    if (hipMalloc(&h->res_mem, resident_bytes(h->rplan)) == hipSuccess && resident_clear(h, h->res_tag) == hipSuccess) return true;
     (void)hipGetLastError();
     if (h->res_mem) (void)hipFree(h->res_mem);
     h->res_mem = nullptr;
@@ -345,33 +349,37 @@ bool resident_ready(les_handle* h) {
     return false;
 }
 
-// Tags of one launch (used once: when they run out the buffers are cleared).
-hipError_t resident_take_tags(les_handle* h, int iters, int K, unsigned& tag) {
+// A launch of up to `iters` iterations with tags of its own (used once: when
+// they run out the buffers are cleared).
+hipError_t resident_launch(les_handle* h, const PBufs& P, double omega, int K, int R, int iters) {
     const unsigned need = resident_tags(iters, K);
     if (h->res_tag > 0xffffffffu - need) {
-        const hipError_t e = launch_fill(h->stream, (float*)h->res_mem, (long long)(resident_bytes(h->rplan) / 4), 0.f);
+        const hipError_t e = resident_clear(h, 1);
         if (e != hipSuccess) return e;
-        h->res_tag = 1;
     }
-    tag = h->res_tag;
+    const hipError_t e = launch_resident(h->g, h->stream, h->rplan, P, h->f.ctl, h->res_mem, omega, K, R, iters, h->res_tag,
+                                         h->res_launches, h->res_spin, h->res_gate);
     h->res_tag += need;
-    return hipSuccess;
+    if (e == hipSuccess) ++h->res_launches;
+    return e;
 }
 
 // A solve waits at most this long for room on the chip (longer than a launch of
 // kResidentIters iterations runs) before it takes its sweep launches.
 constexpr int kResidentPatienceMs = 200;
 
-enum { RES_DONE, RES_BUSY, RES_REFUSED, RES_LOST };
+enum { RES_DONE, RES_BUSY, RES_REFUSED, RES_NO_ROOM, RES_LOST };
 
 // The solve from check interval c + 1 on by resident launches (resident.hip),
 // behind the work on the stream; c and own (resident iterations) are advanced.
-// RES_BUSY: no room on the chip within `patience` ms, and RES_REFUSED: nothing
-// could be launched; the sweeps go on from interval c + 1.
-// RES_LOST: a block waited in vain, as when another process holds part of the
-// chip.  The last two intervals of the launch were then relaxed across borders
-// that may have been old: ph + pd is a start for the sweeps that is as near the
-// solution as they left it, and they repeat those two intervals.
+// RES_BUSY: other threads' launches left no room on the chip for `patience` ms;
+// RES_REFUSED: nothing could be launched; RES_NO_ROOM: not all blocks came to the
+// chip, as when another process holds part of it; the sweeps go on from interval
+// c + 1 in each case.
+// RES_LOST: a block waited in vain.  The last two intervals of the launch were
+// then relaxed across borders that may have been old: ph + pd is a start for the
+// sweeps that is as near the solution as they left it, and they repeat those two
+// intervals.
 int run_resident(les_handle* h, const PBufs& P, int max_iter, int patience, long long& c, long long& own, int& how) {
     hipStream_t st = h->stream;
     const int K = h->prm.check_every, R = h->prm.rebase_every;
@@ -383,11 +391,7 @@ int run_resident(les_handle* h, const PBufs& P, int max_iter, int patience, long
             how = RES_BUSY;
             return LES_OK;
         }
-        unsigned tag = 0;
-        CK(resident_take_tags(h, iters, K, tag));
-        const hipError_t e = timed(
-            h, KN_SOR, kNoTag,
-            [&] { return launch_resident(h->g, st, h->rplan, P, h->f.ctl, h->res_mem, h->prm.omega, K, R, iters, tag, h->res_spin); }, 0);
+        const hipError_t e = timed(h, KN_SOR, kNoTag, [&] { return resident_launch(h, P, h->prm.omega, K, R, iters); }, 0);
         if (e != hipSuccess) {
             (void)hipGetLastError();
             h->resident = false;
@@ -397,6 +401,13 @@ int run_resident(les_handle* h, const PBufs& P, int max_iter, int patience, long
         CK(hipMemcpyAsync(&hc, h->f.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
         CK(hipStreamSynchronize(st));
         share.give();
+        if (hc.lost == kNoRoom) {
+            // try again after 1, 3, 7 .. 63 solves
+            h->res_skip = h->res_pause = std::min(2 * h->res_pause + 1, 63);
+            how = RES_NO_ROOM;
+            return LES_OK;
+        }
+        h->res_pause = 0;
         if (hc.lost) {
             h->resident = false;
             how = RES_LOST;
@@ -538,6 +549,10 @@ int run_solve(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve
     int slot = 0;
     bool pending = false;
     bool resident = !direct && n_checks > 0 && resident_runs(h) && resident_ready(h);
+    if (resident && h->res_skip > 0) {
+        --h->res_skip;
+        resident = false;
+    }
     int patience = kResidentPatienceMs;
     long long own = 0;   // resident iterations
     while (c < n_checks) {
@@ -1375,11 +1390,9 @@ int les_autotune(les_handle* h, int32_t reps, int32_t* chosen, double* us_per_sw
         const int n = std::max(8 * reps, 128);
         float ms = 0.f;
         for (int r = 0; r < 2 && h->resident; ++r) {   // the first launch loads the code
-            unsigned tag = 0;
             CK(launch_ctl_init(s, h->f.ctl, 1e-30, 1 << 30, n));
-            CK(resident_take_tags(h, n, n, tag));
             CK(hipEventRecord(a, s));
-            if (launch_resident(g, s, h->rplan, h->S, h->f.ctl, h->res_mem, 1.0, n, 1 << 30, n, tag, h->res_spin) != hipSuccess) {
+            if (resident_launch(h, h->S, 1.0, n, 1 << 30, n) != hipSuccess) {
                 (void)hipGetLastError();
                 h->resident = false;
             }
@@ -1545,18 +1558,19 @@ int64_t les_bc_range(const les_grid* gr) {
     return (int64_t)nblk(n) * kBlock;   // launch size, padded to whole blocks
 }
 
-// For tests, not part of the public ABI: whether the handle's solves take the
-// resident solver; spin >= -1 bounds its waits to that many polls (-1: the
-// launch is refused), next_tag > 0 clears its buffers and numbers on from there.
-int les_test_resident(les_handle* h, int32_t spin, uint32_t next_tag, int32_t* runs) {
+// For tests, not part of the public ABI: whether the handle's next solve takes
+// the resident solver; spin >= -1 bounds its waits to that many polls (-1: the
+// launch is refused), gate > 0 the roll call (0: it never ends well), next_tag > 0
+// clears its buffers and numbers on from there.
+int les_test_resident(les_handle* h, int32_t spin, int32_t gate, uint32_t next_tag, int32_t* runs) {
     if (!h || !runs) return LES_EINVAL;
     if (spin >= -1) h->res_spin = spin;
+    if (gate >= 0) h->res_gate = gate;
     if (next_tag && resident_runs(h) && resident_ready(h)) {
-        CK(launch_fill(h->stream, (float*)h->res_mem, (long long)(resident_bytes(h->rplan) / 4), 0.f));
+        CK(resident_clear(h, next_tag));
         CK(hipStreamSynchronize(h->stream));
-        h->res_tag = next_tag;
     }
-    *runs = resident_runs(h) ? 1 : 0;
+    *runs = resident_runs(h) && h->res_skip == 0 ? 1 : 0;
     return LES_OK;
 }
 

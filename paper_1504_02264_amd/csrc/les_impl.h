@@ -127,13 +127,14 @@ __host__ __device__ inline bool rebase_due_at(long long cidx, int K, int R) {
 }
 
 // Control block of one pressure solve (device memory).
+enum : unsigned { kLost = 1, kNoRoom = 2 };   // a block waited in vain; not all blocks came
 struct Ctl {
     int done;           // 0 running, 1 converged, 2 hit max_iter, 3 non-finite
     int m;              // SOR iterations completed
     int K;              // check interval
     int max_iter;
     int skip;           // 1: the coming residual check is provably unsuccessful
-    unsigned lost;      // a block of the resident solver waited in vain
+    unsigned lost;      // resident solver: kNoRoom or kLost
     unsigned pad_u[2];
     double tol;
     double rhs2;        // sum rhs^2 (after mean removal)
@@ -198,7 +199,9 @@ struct SolveGraph {
 };
 // Decomposition of a grid for the resident solver (resident.hip): shape -1 if
 // the grid does not fit the chip's registers.
-constexpr int kResSpin = 1 << 21;   // polls of one wait of its blocks: more than a second
+// Polls of one wait of its blocks (more than a second), and of the wait for all
+// of them to come to the chip (some milliseconds).
+constexpr int kResSpin = 1 << 21, kResGateSpin = 1 << 11;
 struct ResPlan {
     int shape;
     int nbx, nby, nbz;   // tiles per axis
@@ -253,7 +256,10 @@ struct les_handle {
     les::ResPlan rplan{};
     void* res_mem = nullptr;
     uint32_t res_tag = 1;
+    uint32_t res_launches = 0;      // since the buffers were cleared
     int res_spin = les::kResSpin;   // polls of one wait (negative: no launch, for tests)
+    int res_gate = les::kResGateSpin;
+    int res_skip = 0, res_pause = 0;   // solves that do not try, after launches that found no room
     // twinned double-buffer comparison solver (twinned.hip): pairs, partials
     void* tw_q = nullptr;
     double* tw_part = nullptr;
@@ -410,7 +416,7 @@ ResPlan resident_plan(const Geo& g, int cus);
 size_t resident_bytes(const ResPlan& p);
 unsigned resident_tags(int iters, int K);
 hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const PBufs& P, Ctl* ctl, void* mem,
-                           double omega, int K, int R, int iters, unsigned tag, int spin);
+                           double omega, int K, int R, int iters, unsigned tag, unsigned launch, int spin, int gate_spin);
 hipError_t launch_project(const Geo& g, hipStream_t st, float* us, float* vs, float* ws,
                           const PBufs& P);
 hipError_t launch_bc(const Geo& g, hipStream_t st, float* u, float* v, float* w);

@@ -45,12 +45,18 @@
 // price of running one at a time, whatever part of the chip they need (the
 // runtime has one queue for them): four threads with a 64x64x32 solve of 400
 // iterations each took 8.0 ms that way and take 2.3 ms side by side, 2.1 ms for
-// one; a solve alone is 20 us shorter as well.  Every wait is bounded.  A
-// wavefront that waits in vain goes on without waiting to the end of its check
-// interval, on borders that may be old and publishing what it makes of them;
-// there its block raises ctl->lost, stores its cells and leaves.  Blocks that
-// wait for it follow within their next interval, so all but the last two
-// intervals of a lost launch are sound (the host goes on with sweep launches).
+// one; a solve alone is 20 us shorter as well.
+//
+// What the host does not know of (another process' launch of this kind) can
+// still hold units for good, so a launch begins with a roll call: unless all
+// blocks come within some milliseconds, all leave again, those that come later
+// too, and nothing has changed (ctl->lost = kNoRoom).  Once all have come, only
+// a suspended queue could keep one from the others; every later wait is bounded
+// all the same.  A wavefront that waits in vain goes on without waiting to the
+// end of its check interval, on borders that may be old and publishing what it
+// makes of them; there its block raises ctl->lost, stores its cells and leaves.
+// Blocks that wait for it follow within their next interval, so all but the last
+// two intervals of a lost launch are sound (the host goes on with sweep launches).
 #include "les_bodies.h"
 
 namespace les {
@@ -69,12 +75,15 @@ struct ResArgs {
     u64* xch;        // [kResSlots][blocks][face words]
     u64* gsum;       // [2][4][blocks]
     u64* xw;         // [2][blocks][west, east][wavefronts][pairs][g]: ghost columns
-    unsigned* xflag; // [blocks][wavefronts][kResPad]: the refresh whose columns are out
+    unsigned* xflag; // [blocks][wavefronts][kResPad]: the patch's last event
+    unsigned* gate;  // blocks that have come, launches so far times blocks
+    u64* verdict;    // (tag0 << 1 | all came) of the last launch
+    unsigned came;   // gate once all blocks of this launch have come
     int nbx, nby, w, gc;   // gc: ghost columns per side
     float omega;
     double omega_d;
     int K, R, cap;
-    int spin;        // polls of one wait
+    int spin, gate_spin;   // polls of one wait, and of the wait for all blocks to come
     unsigned tag0;
 };
 
@@ -708,10 +717,35 @@ struct Resident {
     }
 };
 
+// Whether all blocks of the launch are on the chip.  The block that completes the
+// count says yes, one that has waited long enough says no; the first word stands.
+__device__ __forceinline__ bool roll_call(const ResArgs& a) {
+    bool go = false;
+    if (threadIdx.x < 64) {
+        auto say = [&](bool yes) {
+            u64 v = __hip_atomic_load(a.verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const u64 mine = (u64)a.tag0 << 1 | (yes ? 1 : 0);
+            if (v >> 1 != a.tag0 && __hip_atomic_compare_exchange_strong(a.verdict, &v, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                                         __HIP_MEMORY_SCOPE_AGENT) && !yes)
+                a.ctl->lost = kNoRoom;
+        };
+        if (threadIdx.x == 0 && __hip_atomic_fetch_add(a.gate, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == a.came) say(true);
+#pragma unroll 1
+        for (int spin = 0;; ++spin) {
+            const u64 v = __hip_atomic_load(a.verdict, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            go = v & 1;
+            if (__all(v >> 1 == a.tag0)) break;
+            if (spin == a.gate_spin && threadIdx.x == 0) say(false);
+        }
+    }
+    return __syncthreads_or(go);
+}
+
 template <int RY, int RZ, int GY>
 __global__ __launch_bounds__(kResThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_resident(ResArgs a) {
     __shared__ ResSmem<RY, RZ, GY> sm;
     Ctl* ctl = a.ctl;
+    if (!roll_call(a)) return;
     if (ctl->done) return;   // written by block 0 alone, at its end, after every block has passed here
     typedef Resident<RY, RZ, GY> Res;
     Res w(a, sm);
@@ -857,14 +891,14 @@ ResPlan resident_plan(const Geo& g, int cus) {
 
 size_t resident_bytes(const ResPlan& p) {
     return ((size_t)kResSlots * p.words + 2 * 4 + 2 * (size_t)p.xwords) * p.blocks * sizeof(u64) +
-           (size_t)p.blocks * kResWaves * kResPad * sizeof(unsigned);
+           (size_t)p.blocks * kResWaves * kResPad * sizeof(unsigned) + 2 * 128;
 }
 
 // tags one launch of `iters` iterations may use: two publications each, and at
 // most three sums and one publication per check interval
 unsigned resident_tags(int iters, int K) { return 2u * (unsigned)iters + 4u * (unsigned)(iters / K + 2) + 8u; }
 
-hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const PBufs& P, Ctl* ctl, void* mem, double omega, int K, int R, int iters, unsigned tag, int spin) {
+hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const PBufs& P, Ctl* ctl, void* mem, double omega, int K, int R, int iters, unsigned tag, unsigned launch, int spin, int gate_spin) {
     if (spin < 0) return hipErrorInvalidValue;
     ResArgs a{};
     a.g = g;
@@ -874,6 +908,9 @@ hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const
     a.gsum = a.xch + (size_t)kResSlots * p.words * p.blocks;
     a.xw = a.gsum + 2 * 4 * (size_t)p.blocks;
     a.xflag = (unsigned*)(a.xw + 2 * (size_t)p.xwords * p.blocks);
+    a.gate = a.xflag + (size_t)p.blocks * kResWaves * kResPad;
+    a.verdict = (u64*)(a.gate + 32);
+    a.came = (launch + 1) * p.blocks + (gate_spin == 0 ? 1 : 0);   // 0: out of reach, for tests
     a.nbx = p.nbx;
     a.nby = p.nby;
     a.w = p.w;
@@ -884,6 +921,7 @@ hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const
     a.R = R;
     a.cap = iters;
     a.spin = spin;
+    a.gate_spin = gate_spin;
     a.tag0 = tag;
     return kShapes[p.shape].start(a, p.blocks, st);
 }

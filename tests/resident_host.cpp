@@ -6,11 +6,12 @@
 // it moves by one collective operation only when all others wait.  What the
 // kernel computes must not depend on it.
 //
-//   resident_host nx ny nz K R max_iter tag0 tol spin victim...
+//   resident_host nx ny nz K R max_iter tag0 tol spin gate victim...
 //
-// victim -1: blocks run in turn; spin: polls of one wait (0: the kernel's own
-// bound).  Prints, for each victim, a line with the control block and checksums
-// of ph, pd and r0 of both colours.
+// victim -1: blocks run in turn; spin, gate: polls of one wait and of the roll
+// call (0: the kernel's own bounds; with a bound for the roll call the victim
+// comes later than that).  Prints, for each victim, a line with the control block
+// and checksums of ph, pd and r0 of both colours.
 #include <hip/hip_runtime.h>
 #include <ucontext.h>
 
@@ -54,7 +55,7 @@ thread_local Block* blk;
 
 struct Grid {
     unsigned n;
-    int victim, turn = 0;
+    int victim, turn = 0, late = 0;   // late: rounds of polls before the victim starts
     std::function<void()> body;
     std::vector<char> done, waits;
     std::mutex m;
@@ -70,13 +71,15 @@ struct Grid {
             const int c = (int)((b + q) % n);
             if (!done[c] && !waits[c] && c != victim) return c;
         }
-        if (victim >= 0 && !done[victim]) return victim;
+        const bool first = victim >= 0 && late > 0 && n > 1;   // the victim has yet to start, and is late
+        if (victim >= 0 && !done[victim] && !first) return victim;
+        if (first) --late;
         std::fill(waits.begin(), waits.end(), 0);
         for (unsigned q = 1; q <= n; ++q) {
             const int c = (int)((b + q) % n);
-            if (!done[c]) return c;
+            if (!done[c] && (c != victim || !first)) return c;
         }
-        return b;
+        return first ? victim : b;
     }
     void yield(int b, bool waiting) {
         std::unique_lock<std::mutex> l(m);
@@ -205,12 +208,27 @@ T move(Op op, T v, int arg) {
     std::memcpy(&v, &b, sizeof v);
     return v;
 }
+template <class T, class S>
+T add(T* p, S v) {
+    const T old = *p;
+    *p += v;
+    return old;
+}
+template <class T>
+bool swap(T* p, T* old, T v) {
+    if (*p != *old) {
+        *old = *p;
+        return false;
+    }
+    *p = v;
+    return true;
+}
 template <class T>
 T zero() {   // an operation no host run reaches
     std::abort();
     return T();
 }
-int g_victim = -1;
+int g_victim = -1, g_late = 0;
 
 }  // namespace host
 
@@ -233,6 +251,8 @@ int g_victim = -1;
 #define __syncthreads_or(v) ((int)host::collective(host::OR, (v) ? 1 : 0))
 #define __hip_atomic_load(p, ...) (*(p))
 #define __hip_atomic_store(p, v, ...) ((void)(*(p) = (v)))
+#define __hip_atomic_fetch_add(p, v, ...) (host::add(p, v))
+#define __hip_atomic_compare_exchange_strong(p, old, v, ...) (host::swap(p, old, v))
 #define __longlong_as_double(v) host::bits<double>(v)
 #define __double_as_longlong(v) host::bits<long long>(v)
 #define __int_as_float(v) host::bits<float>(v)
@@ -262,6 +282,7 @@ extern "C" hipError_t hipLaunchKernel(const void* f, dim3 blocks, dim3 threads, 
     host::Grid grid;
     grid.n = blocks.x;
     grid.victim = host::g_victim;
+    grid.late = host::g_late;
     grid.done.assign(grid.n, 0);
     grid.waits.assign(grid.n, 0);
     grid.turn = grid.victim == 0 && grid.n > 1 ? 1 : 0;
@@ -275,7 +296,7 @@ extern "C" hipError_t hipLaunchKernel(const void* f, dim3 blocks, dim3 threads, 
 }
 
 int main(int argc, char** argv) {
-    if (argc < 11) return 2;
+    if (argc < 12) return 2;
     auto num = [&](int q) { return std::atoll(argv[q]); };
     les::Geo g{};
     g.nx = (int)num(1);
@@ -295,8 +316,9 @@ int main(int argc, char** argv) {
     g.outflow = 1;
     const les::ResPlan p = les::resident_plan(g, 256);
     if (p.shape < 0) return 4;
-    for (int arg = 10; arg < argc; ++arg) {
+    for (int arg = 11; arg < argc; ++arg) {
         host::g_victim = (int)num(arg);
+        host::g_late = num(10) ? 4 * (int)num(10) : 0;
         std::vector<float> mem[8];
         for (auto& v : mem) v.assign(g.ctot, 0.f);
         les::PBufs P{};
@@ -327,7 +349,8 @@ int main(int argc, char** argv) {
         ctl.tol = std::atof(argv[8]);
         ctl.rhs2 = rhs2;
         std::vector<unsigned long long> x(les::resident_bytes(p) / 8 + 1, 0);
-        les::launch_resident(g, nullptr, p, P, &ctl, x.data(), 1.8, K, R, max_iter, (unsigned)num(7), num(9) ? (int)num(9) : les::kResSpin);
+        les::launch_resident(g, nullptr, p, P, &ctl, x.data(), 1.8, K, R, max_iter, (unsigned)num(7), 0,
+                             num(9) ? (int)num(9) : les::kResSpin, num(10) ? (int)num(10) : 1 << 30);
         std::printf("blocks %u ghosts %d m %d done %d lost %u resid %.17g", p.blocks, p.g, ctl.m, ctl.done, ctl.lost, ctl.resid);
         for (int q = 0; q < 6; ++q) {
             unsigned long long h = 1469598103934665603ull;

@@ -18,15 +18,15 @@ from test_gpu_resident import same
 
 pytestmark = pytest.mark.gpu
 
-SPIN = 1 << 21   # the solver's own bound of a wait
+SPIN, GATE = 1 << 21, 1 << 11   # the solver's own bounds of a wait and of the roll call
 SPACING = (2.0, 3.0, 1.5)
 
 
-def resident(g, spin=-2, tag=0):
+def resident(g, spin=-2, gate=-1, tag=0):
     f = les.lib().les_test_resident
-    f.argtypes = [C.c_void_p, C.c_int32, C.c_uint32, C.POINTER(C.c_int32)]
+    f.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_uint32, C.POINTER(C.c_int32)]
     runs = C.c_int32()
-    assert f(g.h, spin, tag, C.byref(runs)) == les.LES_OK
+    assert f(g.h, spin, gate, tag, C.byref(runs)) == les.LES_OK
     return runs.value
 
 
@@ -130,6 +130,24 @@ def test_refused_launch():
         resident(g, spin=-1)
         same(g.pressure_solve(rhs, p0, max_iter=300), ref.pressure_solve(rhs, p0, max_iter=300))
         assert not resident(g, spin=SPIN)
+    finally:
+        g.close()
+        ref.close()
+
+
+def test_no_room_on_the_chip():
+    """A roll call that ends too soon: the sweeps run the solve from its start, the
+    handle tries again after one solve, then after three, and is resident again."""
+    shape = (150, 33, 11)
+    rhs, p0 = inputs(shape)
+    g, ref = make(shape), make(shape, 0)
+    try:
+        want = ref.pressure_solve(rhs, p0, max_iter=300)
+        tries = ((0, True), (0, False), (0, True), (0, False), (0, False), (0, False), (GATE, True), (GATE, True))
+        for gate, now in tries:
+            assert resident(g, gate=gate) == now
+            same(g.pressure_solve(rhs, p0, max_iter=300), want)
+        assert resident(g)
     finally:
         g.close()
         ref.close()

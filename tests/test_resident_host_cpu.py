@@ -23,8 +23,8 @@ def exe(tmp_path_factory):
     return out
 
 
-def lines(exe, shape, K, R, max_iter, victims, tag=1, tol=1e-12, spin=0):
-    r = subprocess.run([exe] + [str(v) for v in (*shape, K, R, max_iter, tag, tol, spin, *victims)], capture_output=True, text=True,
+def lines(exe, shape, K, R, max_iter, victims, tag=1, tol=1e-12, spin=0, gate=0):
+    r = subprocess.run([exe] + [str(v) for v in (*shape, K, R, max_iter, tag, tol, spin, gate, *victims)], capture_output=True, text=True,
                        timeout=300)
     assert r.returncode == 0, r.stdout[-2000:] + r.stderr[-2000:]
     return r.stdout.splitlines()
@@ -65,3 +65,16 @@ def test_waits_in_vain(exe, shape, K, R):
     for out in lines(exe, shape, K, R, 40, (-1, 0, 1), spin=1):
         assert " lost 1 " in out and out.endswith("finite 1"), out
         assert 0 < int(out.split(" m ")[1].split()[0]) <= 40, out
+
+
+@pytest.mark.parametrize("shape", [(150, 8, 4), (30, 17, 4)])
+def test_roll_call(exe, shape):
+    """A launch whose blocks do not all come in time runs whole or not at all,
+    whichever block is late."""
+    victims = (-1, 0, 1)
+    whole = lines(exe, shape, 4, 32, 12, victims)
+    early = lines(exe, shape, 4, 32, 12, victims, gate=1)
+    assert len(set(whole)) == 1 and " lost 0 " in whole[0] and " m 12 " in whole[0]
+    none = {o for o in early if o not in whole}
+    assert len(none) == 1, early
+    assert " m 0 done 0 lost 2 resid 0 " in none.pop(), early
