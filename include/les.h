@@ -327,9 +327,10 @@ int les_get_ghosted(les_handle* h, float* u, float* v, float* w);
  * launches.  Families: 0 nu_t, 1 tendency, 2 inflow, 3 rhs, 4 SOR sweep
  * launch (a half-sweep, a whole iteration with the fused variants 8-11,
  * two with 12-13; solves by the resident kernel: its whole time, checks and
- * folds included, and every iteration counted as a launch), 5 residual check (sampled like the sweeps: the launches
- * count is that of the sampled intervals), 6 rebase, 7 projection, 8
- * boundary refresh.  reset = 1 clears the counters after reading. */
+ * folds included, and every iteration counted as a launch; sweep launches
+ * that come before it in such a solve are not counted), 5 residual check
+ * (sampled like the sweeps: the launches count is that of the sampled
+ * intervals), 6 rebase, 7 projection, 8 boundary refresh.  reset = 1 clears the counters after reading. */
 #define LES_NUM_KERNELS 9
 typedef struct {
     double ms[LES_NUM_KERNELS];
@@ -362,10 +363,13 @@ int les_get_timing(les_handle* h, les_timing* out, int32_t reset);
  * launch for thousands of iterations, with the same arithmetic and the same
  * results bit for bit; sweep launches serve the other grids, ensembles and
  * the allocation-free solve.  les_set_sor_variant turns it off for the
- * handle (its solves then use the variant asked for), les_autotune turns it
- * on where it is faster than every variant.  Its face buffers (tens of MB at
- * most) are allocated at the handle's first solve; without the memory for
- * them the handle uses its sweep variant.  A launch needs compute units for
+ * handle (its solves then use the variant asked for, as does a handle that is
+ * given another's *chosen), les_autotune times both and turns it on where it
+ * is faster than the variant it chose: for whole solves, or after their first
+ * 512 iterations, in which the base is refreshed often and which the variant
+ * then takes.  Its face buffers (tens of MB at most) are allocated at the
+ * handle's first solve; without the memory for them the handle uses its sweep
+ * variant.  A launch needs compute units for
  * itself (one for a block of 128 x 8 x 4 cells to one of 128 x 24 x 16, as
  * the grid asks): solves of several threads of a process run side by side
  * while they all fit and in turn otherwise, and one that waits longer than
@@ -377,8 +381,8 @@ int les_get_timing(les_handle* h, les_timing* out, int32_t reset);
  * the handle to its sweep launches until les_autotune.
  *
  * Autotuner: times every variant for reps back-to-back pairs of launches
- * on this handle's grid, keeps the fastest for all later solves of the
- * handle and reports its index in *chosen (nullable) and the per-variant
+ * on this handle's grid, keeps the fastest for all later sweep launches of
+ * the handle and reports its index in *chosen (nullable) and the per-variant
  * microseconds per half-sweep (for 8-11: half a fused iteration; for
  * 12-13 a quarter of a launch; 0 when not timed because check_every does
  * not allow the variant) in

@@ -553,10 +553,13 @@ int run_solve(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve
         --h->res_skip;
         resident = false;
     }
+    // where the sweeps are faster while folds are frequent (les_autotune), they
+    // take the early intervals
+    const long long c_res = resident && !h->res_early ? std::min(early_end, n_checks) : 0;
     int patience = kResidentPatienceMs;
     long long own = 0;   // resident iterations
     while (c < n_checks) {
-        if (resident) {
+        if (resident && c >= c_res) {
             int how = RES_DONE;
             const int rc = run_resident(h, P, max_iter, patience, c, own, how);
             if (rc != LES_OK) return rc;
@@ -577,7 +580,7 @@ int run_solve(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve
                 bi = 0;
             }
         }
-        const long long nb = std::min<long long>(std::min(kBatches[bi], batch_cap), n_checks - c);
+        const long long nb = std::min<long long>(std::min(kBatches[bi], batch_cap), (c < c_res ? c_res : n_checks) - c);
         long long q = 0;
         while (q < nb) {
             const long long c0 = c + q;   // intervals c0+1, ...
@@ -604,6 +607,7 @@ int run_solve(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve
     CK(hipMemcpyAsync(h->h_ctl, ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
     CK(hipStreamSynchronize(st));
     const Ctl& hc = *h->h_ctl;
+    h->res_iters += own;
     if (timing) {
         // every resident iteration is timed: sampled sweep launches beside them
         // (other units) are left out, as is a resident launch that did none
@@ -1334,7 +1338,10 @@ int les_get_ghosted(les_handle* h, float* u, float* v, float* w) {
     return LES_OK;
 }
 
-int les_autotune(les_handle* h, int32_t reps, int32_t* chosen, double* us_per_sweep) {
+}  // extern "C"
+
+namespace les {
+int autotune_sweeps(les_handle* h, int32_t reps, int32_t* chosen, double* us_per_sweep) {
     if (!h || reps < 1 || reps > 1000) return LES_EINVAL;
     int rc = ensure_solve_arena(h);
     if (rc != LES_OK) return rc;
@@ -1382,26 +1389,6 @@ int les_autotune(les_handle* h, int32_t reps, int32_t* chosen, double* us_per_sw
             best_v = v;
         }
     }
-    // the resident solver on the same zero system: one interval of reps
-    // iterations and its check per launch (it stops there, the norm being 0)
-    h->resident = h->rplan.shape >= 0;
-    ChipShare share(h->device, h->cus);
-    if (resident_runs(h) && resident_ready(h) && share.take(h->rplan.blocks, kResidentPatienceMs)) {
-        const int n = std::max(8 * reps, 128);
-        float ms = 0.f;
-        for (int r = 0; r < 2 && h->resident; ++r) {   // the first launch loads the code
-            CK(launch_ctl_init(s, h->f.ctl, 1e-30, 1 << 30, n));
-            CK(hipEventRecord(a, s));
-            if (resident_launch(h, h->S, 1.0, n, 1 << 30, n) != hipSuccess) {
-                (void)hipGetLastError();
-                h->resident = false;
-            }
-            CK(hipEventRecord(b, s));
-            CK(hipEventSynchronize(b));
-            CK(hipEventElapsedTime(&ms, a, b));
-        }
-        if (1e3 * ms / (2.0 * n) >= best) h->resident = false;
-    }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     for (int c = 0; c < 2; ++c) CK(launch_fill(s, h->S.pd[c], g.ctot, 0.f));
@@ -1410,6 +1397,85 @@ int les_autotune(les_handle* h, int32_t reps, int32_t* chosen, double* us_per_sw
     h->sor_variant = best_v;
     if (chosen) *chosen = best_v;
     return LES_OK;
+}
+}  // namespace les
+
+namespace {
+
+// Wall time (s) of a solve of n iterations checked every K, resident or by the
+// sweeps, on a zero system of norm 1 that never ends early: the best of `times`.
+// ran: as asked (other threads may have held the chip).
+int time_solve(les_handle* h, bool resident, int K, int n, int times, double& best, bool& ran) {
+    hipStream_t s = h->stream;
+    const les_params prm = h->prm;
+    h->prm.timing = 0;
+    h->prm.check_every = K;
+    h->resident = resident;
+    h->res_early = true;
+    h->res_skip = 0;
+    auto once = [&]() -> int {
+        CK(launch_ctl_init(s, h->f.ctl, -1.0, n, K));
+        h->h_ctl->rhs2 = 1.0;
+        CK(hipMemcpyAsync(&h->f.ctl->rhs2, &h->h_ctl->rhs2, sizeof(double), hipMemcpyHostToDevice, s));
+        CK(hipStreamSynchronize(s));
+        const int64_t iters = h->res_iters;
+        const auto t = std::chrono::steady_clock::now();
+        const int rc = run_solve(h, h->S, -1.0, n, nullptr, !resident);
+        const double dt = std::chrono::duration<double>(std::chrono::steady_clock::now() - t).count();
+        ran = ran && h->res_iters - iters == (resident ? n : 0);
+        best = std::min(best, dt);
+        return rc < 0 ? rc : LES_OK;
+    };
+    best = 1e300;
+    ran = true;
+    int rc = LES_OK;
+    for (int q = 0; q < times && rc == LES_OK; ++q) rc = once();
+    h->prm = prm;
+    return rc;
+}
+
+// Whether the handle's solves take the resident solver, and from the start or
+// after the early folds: both forms are timed over some of the handle's own fold
+// cycles, and, where the sweeps win there, over 64 iterations with one fold.
+// The resident fold goes through memory past the caches (130 us against 60 at
+// 300x300x90), so with a check every 4 iterations and a fold every 8 the largest
+// patch is slower than tuned sweeps there (300x300x90, 400 iterations: 10.7 ms
+// against 10.4; 256x256x64: 9.0 against 8.0), though faster by a third beyond.
+int choose_resident(les_handle* h) {
+    h->resident = h->rplan.shape >= 0;
+    h->res_early = true;
+    if (!resident_runs(h) || !resident_ready(h)) return LES_OK;
+    hipStream_t s = h->stream;
+    const long long n_col = h->g.ctot;
+    for (int c = 0; c < 2; ++c)
+        for (float* q : {h->S.ph[c], h->S.pd[c], h->S.rhs[c]}) CK(launch_fill(s, q, n_col, 0.f));
+    const int K = h->prm.check_every, cycle = (K >= 8 ? 1 : 8 / K) * K;
+    bool resident = true, early = true, ran = true, ran_s = true;
+    double t_res = 0.0, t_sweeps = 0.0;
+    int rc = LES_OK;
+    auto faster = [&](int interval, int n, int times) {
+        rc = time_solve(h, true, interval, n, times, t_res, ran);
+        if (rc == LES_OK && ran) rc = time_solve(h, false, interval, n, times, t_sweeps, ran_s);
+        return !ran || t_res < t_sweeps;   // without a measurement: as an untuned handle
+    };
+    const bool any = cycle <= kEarlyFoldIters;   // early folds
+    if (any) early = faster(K, cycle * std::max(1, 32 / cycle), 2);   // the first run loads the code
+    if (rc == LES_OK && !(any && early)) resident = faster(64, 64, any ? 1 : 2);
+    for (int c = 0; c < 2; ++c)
+        for (float* q : {h->S.pd[c], h->S.pa[c]}) CK(launch_fill(s, q, n_col, 0.f));
+    CK(hipStreamSynchronize(s));
+    h->resident = rc == LES_OK && resident;
+    h->res_early = early;
+    return rc;
+}
+
+}  // namespace
+
+extern "C" {
+
+int les_autotune(les_handle* h, int32_t reps, int32_t* chosen, double* us_per_sweep) {
+    const int rc = autotune_sweeps(h, reps, chosen, us_per_sweep);
+    return rc == LES_OK ? choose_resident(h) : rc;
 }
 
 int les_set_sor_variant(les_handle* h, int32_t variant) {
@@ -1560,12 +1626,14 @@ int64_t les_bc_range(const les_grid* gr) {
 
 // For tests, not part of the public ABI: whether the handle's next solve takes
 // the resident solver; spin >= -1 bounds its waits to that many polls (-1: the
-// launch is refused), gate > 0 the roll call (0: it never ends well), next_tag > 0
-// clears its buffers and numbers on from there.
-int les_test_resident(les_handle* h, int32_t spin, int32_t gate, uint32_t next_tag, int32_t* runs) {
+// launch is refused), gate > 0 the roll call (0: it never ends well), early >= 0
+// says whether it takes the early intervals, next_tag > 0 clears its buffers and
+// numbers on from there.
+int les_test_resident(les_handle* h, int32_t spin, int32_t gate, int32_t early, uint32_t next_tag, int32_t* runs) {
     if (!h || !runs) return LES_EINVAL;
     if (spin >= -1) h->res_spin = spin;
     if (gate >= 0) h->res_gate = gate;
+    if (early >= 0) h->res_early = early != 0;
     if (next_tag && resident_runs(h) && resident_ready(h)) {
         CK(resident_clear(h, next_tag));
         CK(hipStreamSynchronize(h->stream));

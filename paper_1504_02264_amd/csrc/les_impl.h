@@ -252,6 +252,8 @@ struct les_handle {
     uint64_t sgraph_tick = 0;
     // resident solver: whether solves take it, its plan, face buffers and next tag
     bool resident = false;
+    bool res_early = true;          // also while folds are frequent (les_autotune)
+    int64_t res_iters = 0;          // iterations it has done
     int cus = 0;                    // compute units of the device
     les::ResPlan rplan{};
     void* res_mem = nullptr;
@@ -410,6 +412,8 @@ private:
     long long held_ = 0;
     ChipShare* next_ = nullptr;
 };
+// les_autotune's part that times the sweep variants
+int autotune_sweeps(les_handle* h, int32_t reps, int32_t* chosen, double* us_per_sweep);
 // resident solver (resident.hip): up to `iters` more iterations of the solve
 // ctl describes (stopping tests included), the face buffers in mem
 ResPlan resident_plan(const Geo& g, int cus);

@@ -22,11 +22,11 @@ SPIN, GATE = 1 << 21, 1 << 11   # the solver's own bounds of a wait and of the r
 SPACING = (2.0, 3.0, 1.5)
 
 
-def resident(g, spin=-2, gate=-1, tag=0):
+def resident(g, spin=-2, gate=-1, early=-1, tag=0):
     f = les.lib().les_test_resident
-    f.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_uint32, C.POINTER(C.c_int32)]
+    f.argtypes = [C.c_void_p, C.c_int32, C.c_int32, C.c_int32, C.c_uint32, C.POINTER(C.c_int32)]
     runs = C.c_int32()
-    assert f(g.h, spin, gate, tag, C.byref(runs)) == les.LES_OK
+    assert f(g.h, spin, gate, early, tag, C.byref(runs)) == les.LES_OK
     return runs.value
 
 
@@ -227,3 +227,51 @@ def test_solves_beside_a_persistent_ensemble():
         eb.close()
         for g in a + b + gs:
             g.close()
+
+
+@pytest.mark.parametrize("shape", [(64, 33, 11), (150, 33, 11), (70, 131, 67)])
+@pytest.mark.parametrize("K,tol", [(3, 1e-9), (4, 1e-9), (4, 1e-2), (16, 1e-9), (64, 1e-9), (600, 1e-9)])
+def test_sweeps_take_the_early_intervals(shape, K, tol):
+    """Sweep launches for the first 512 iterations (whole intervals) and the
+    resident solver beyond, for solves that end before, at and after the change."""
+    rhs, p0 = inputs(shape)
+    kw = dict(check_every=K, rebase_every=max(1, 128 // K))
+    g, ref = make(shape, timing=1, **kw), make(shape, 1, **kw)
+    try:
+        assert resident(g, early=0)
+        g.pressure_solve(rhs, p0, tol=tol, max_iter=1)
+        for n in (1, 300, 512, 513, 517, 1300):
+            g.get_timing(reset=True)
+            got = g.pressure_solve(rhs, p0, tol=tol, max_iter=n)
+            same(got, ref.pressure_solve(rhs, p0, tol=tol, max_iter=n))
+            beyond = got[1]["iters"] - 512 // K * K
+            if beyond > 0:
+                assert g.get_timing()["sor"][1] == beyond
+        g.get_timing(reset=True)
+        assert resident(g, early=1)
+        same(g.pressure_solve(rhs, p0, tol=tol, max_iter=300), ref.pressure_solve(rhs, p0, tol=tol, max_iter=300))
+    finally:
+        g.close()
+        ref.close()
+
+
+@pytest.mark.parametrize("shape", [(33, 17, 9), (150, 33, 11), (256, 256, 64)])
+@pytest.mark.parametrize("K", [3, 4, 64, 1000])
+def test_tuned_solves_equal_sweep_launches(shape, K):
+    """Whatever form the autotuner keeps, from a workspace that has held a
+    right-hand side that is not finite."""
+    rhs, p0 = inputs(shape)
+    kw = dict(check_every=K, rebase_every=max(1, 128 // K))
+    g, ref = make(shape, **kw), make(shape, 1, **kw)
+    try:
+        bad = rhs.copy()
+        bad[1, 2, 3] = np.nan
+        with pytest.raises(les.LesError):
+            g.pressure_solve(bad, p0)
+        v, us = g.autotune(reps=3)
+        print(f"[tuned] {shape} K={K} variant {v} resident {resident(g)}", flush=True)
+        for n in (200, 900):
+            same(g.pressure_solve(rhs, p0, tol=1e-9, max_iter=n), ref.pressure_solve(rhs, p0, tol=1e-9, max_iter=n))
+    finally:
+        g.close()
+        ref.close()
