@@ -1124,9 +1124,9 @@ int les_ensemble_autotune(les_ensemble* e, int32_t reps) {
     for (int q = 0; q < n; ++q) {
         les_handle* h = e->members[q];
         if (!h->solve_arena) {
-            les_solve_stats st{};
-            (void)st;
-            int rc = les_autotune(h, 1, nullptr, nullptr);   // allocates the scratch system
+            // allocates the scratch system (and not the resident solver's
+            // buffers, which an ensemble does not use)
+            int rc = autotune_sweeps(h, 1, nullptr, nullptr);
             if (rc != LES_OK) return ens_err(e, rc, "member scratch allocation");
         }
     }

@@ -9,6 +9,7 @@ import threading
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import paper_1504_02264_amd as les
@@ -275,3 +276,20 @@ def test_tuned_solves_equal_sweep_launches(shape, K):
     finally:
         g.close()
         ref.close()
+
+
+def test_ensemble_autotune_leaves_members_without_face_buffers():
+    """An ensemble never uses them: a member allocates them at its own first solve."""
+    shape = (150, 150, 90)
+    g = make(shape)
+    e = les.Ensemble([g])
+    try:
+        e.autotune(reps=1)
+        before = torch.cuda.mem_get_info()[0]
+        rhs, p0 = inputs(shape)
+        g.pressure_solve(rhs, p0, max_iter=1)
+        assert torch.cuda.mem_get_info()[0] < before
+        assert resident(g)
+    finally:
+        e.close()
+        g.close()
