@@ -364,6 +364,17 @@ hipError_t resident_launch(les_handle* h, const PBufs& P, double omega, int K, i
     return e;
 }
 
+// Solves capped at a few iterations take their sweep launches: loading the tiles
+// and a check through memory cost more.  The sweeps always run whole check
+// intervals, so it is those that count: up to two iterations (one: 128x128x64 110
+// us by sweeps, 128 resident, 256x256x64 184 and 206; two: 117 and 128, 197 and
+// 214; three: 155 and 146, 263 and 241), or four in a single interval, with its
+// one check, and the smallest patch (64x64x32: 99 and 104 us, 128x128x64 129 and
+// 128; but 187x131x67, a larger patch, 156 and 146).
+bool resident_too_short(const les_handle* h, long long n_checks) {
+    const long long iters = n_checks * h->prm.check_every;
+    return iters <= (n_checks == 1 && h->rplan.shape == 0 ? 4 : 2);
+}
 // A solve waits at most this long for room on the chip (longer than a launch of
 // kResidentIters iterations runs) before it takes its sweep launches.
 constexpr int kResidentPatienceMs = 200;
@@ -548,7 +559,7 @@ int run_solve(les_handle* h, const PBufs& P, double tol, int max_iter, les_solve
     int bi = 0;
     int slot = 0;
     bool pending = false;
-    bool resident = !direct && n_checks > 0 && resident_runs(h) && resident_ready(h);
+    bool resident = !direct && resident_runs(h) && !resident_too_short(h, n_checks) && resident_ready(h);
     if (resident && h->res_skip > 0) {
         --h->res_skip;
         resident = false;

@@ -287,9 +287,31 @@ def test_ensemble_autotune_leaves_members_without_face_buffers():
         e.autotune(reps=1)
         before = torch.cuda.mem_get_info()[0]
         rhs, p0 = inputs(shape)
-        g.pressure_solve(rhs, p0, max_iter=1)
+        g.pressure_solve(rhs, p0, max_iter=4)
         assert torch.cuda.mem_get_info()[0] < before
         assert resident(g)
     finally:
         e.close()
         g.close()
+
+
+@pytest.mark.parametrize("shape,patch", [((33, 17, 9), 4), ((150, 33, 11), 4), ((187, 131, 67), 24)])
+@pytest.mark.parametrize("K", [1, 2, 4, 8])
+def test_solves_of_a_few_iterations(shape, patch, K):
+    """Whole check intervals of up to two iterations (one interval of up to four
+    with the smallest patch) take the sweep launches, of which one interval in
+    eight is timed, from the first one on; longer solves are resident."""
+    rhs, p0 = inputs(shape)
+    g, ref = make(shape, check_every=K, timing=1), make(shape, 0, check_every=K, timing=1)
+    try:
+        for n in (1, 2, 3, 4, 5):
+            for h in (g, ref):
+                h.get_timing(reset=True)
+            same(g.pressure_solve(rhs, p0, tol=1e-9, max_iter=n), ref.pressure_solve(rhs, p0, tol=1e-9, max_iter=n))
+            sweeps = ref.get_timing()["sor"][1]
+            whole = -(-n // K) * K
+            few = whole <= (4 if n <= K and patch == 4 else 2)
+            assert g.get_timing()["sor"][1] == (sweeps if few else n)
+    finally:
+        g.close()
+        ref.close()
