@@ -1134,7 +1134,10 @@ int ensure_ws(lesnet* n, int B, int D, int H, int W) {
         *r.first = c;
         c += (r.second + 255) & ~(size_t)255;
     }
+    // on the null stream, behind whatever runs there, and not waited for by the
+    // streams the network runs on
     NCK(hipMemset(p, 0, total));
+    NCK(hipStreamSynchronize(nullptr));
     n->B = B;
     n->D = D;
     n->H = H;
