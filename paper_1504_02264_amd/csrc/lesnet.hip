@@ -1579,12 +1579,14 @@ int lesnet_num_params(const lesnet* n, int64_t* count) {
 
 int lesnet_get_params(lesnet* n, float* host, int64_t count) {
     if (!n || !host || count != n->nparam) return LES_EINVAL;
+    NCK(hipDeviceSynchronize());   // the network's calls may run on a stream of their own
     NCK(hipMemcpy(host, n->w, (size_t)count * 4, hipMemcpyDeviceToHost));
     return LES_OK;
 }
 
 int lesnet_set_params(lesnet* n, const float* host, int64_t count) {
     if (!n || !host || count != n->nparam) return LES_EINVAL;
+    NCK(hipDeviceSynchronize());   // the network's calls may run on a stream of their own
     NCK(hipMemcpy(n->w, host, (size_t)count * 4, hipMemcpyHostToDevice));
     n->layout_fresh = false;
     return LES_OK;
@@ -1592,6 +1594,7 @@ int lesnet_set_params(lesnet* n, const float* host, int64_t count) {
 
 int lesnet_get_grads(lesnet* n, float* host, int64_t count) {
     if (!n || !host || count != n->nparam) return LES_EINVAL;
+    NCK(hipDeviceSynchronize());   // the network's calls may run on a stream of their own
     NCK(hipMemcpy(host, n->g, (size_t)count * 4, hipMemcpyDeviceToHost));
     return LES_OK;
 }
