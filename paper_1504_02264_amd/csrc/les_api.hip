@@ -1414,9 +1414,9 @@ int autotune_sweeps(les_handle* h, int32_t reps, int32_t* chosen, double* us_per
 namespace {
 
 // Wall time (s) of a solve of n iterations checked every K, resident or by the
-// sweeps, on a zero system of norm 1 that never ends early: the best of `times`.
-// ran: as asked (other threads may have held the chip).
-int time_solve(les_handle* h, bool resident, int K, int n, int times, double& best, bool& ran) {
+// sweeps, on a zero system of norm 1 that never ends early; the better one of
+// this and `best`.  ran: as asked (other threads may have held the chip).
+int time_solve(les_handle* h, bool resident, int K, int n, double& best, bool& ran) {
     hipStream_t s = h->stream;
     const les_params prm = h->prm;
     h->prm.timing = 0;
@@ -1437,10 +1437,7 @@ int time_solve(les_handle* h, bool resident, int K, int n, int times, double& be
         best = std::min(best, dt);
         return rc < 0 ? rc : LES_OK;
     };
-    best = 1e300;
-    ran = true;
-    int rc = LES_OK;
-    for (int q = 0; q < times && rc == LES_OK; ++q) rc = once();
+    const int rc = once();
     h->prm = prm;
     return rc;
 }
@@ -1461,17 +1458,21 @@ int choose_resident(les_handle* h) {
     for (int c = 0; c < 2; ++c)
         for (float* q : {h->S.ph[c], h->S.pd[c], h->S.rhs[c]}) CK(launch_fill(s, q, n_col, 0.f));
     const int K = h->prm.check_every, cycle = (K >= 8 ? 1 : 8 / K) * K;
-    bool resident = true, early = true, ran = true, ran_s = true;
-    double t_res = 0.0, t_sweeps = 0.0;
+    bool resident = true, early = true, ran = true;
     int rc = LES_OK;
-    auto faster = [&](int interval, int n, int times) {
-        rc = time_solve(h, true, interval, n, times, t_res, ran);
-        if (rc == LES_OK && ran) rc = time_solve(h, false, interval, n, times, t_sweeps, ran_s);
+    // once, and if it is not clear then, the better of two (a process' first
+    // launch also loads the code)
+    auto faster = [&](int interval, int n) {
+        double t_res = 1e300, t_sweeps = 1e300;
+        for (int q = 0; q < 2 && rc == LES_OK && ran && !(t_res < 0.9 * t_sweeps); ++q) {
+            rc = time_solve(h, true, interval, n, t_res, ran);
+            if (rc == LES_OK && ran) rc = time_solve(h, false, interval, n, t_sweeps, ran);
+        }
         return !ran || t_res < t_sweeps;   // without a measurement: as an untuned handle
     };
     const bool any = cycle <= kEarlyFoldIters;   // early folds
-    if (any) early = faster(K, cycle * std::max(1, 32 / cycle), 2);   // the first run loads the code
-    if (rc == LES_OK && !(any && early)) resident = faster(64, 64, any ? 1 : 2);
+    if (any) early = faster(K, cycle * std::max(1, 32 / cycle));
+    if (rc == LES_OK && !(any && early)) resident = faster(64, 64);
     for (int c = 0; c < 2; ++c)
         for (float* q : {h->S.pd[c], h->S.pa[c]}) CK(launch_fill(s, q, n_col, 0.f));
     CK(hipStreamSynchronize(s));
