@@ -22,7 +22,9 @@ Prints ONE JSON line:
              `traffic` is the measured HBM bytes (rocprofv3 FETCH_SIZE +
              WRITE_SIZE, copy-calibrated) from the summaries in profiles/.
              Where the autotuner keeps the resident solver, its flops
-             (13 per cell and iteration) against the vector units.
+             (13 per cell and iteration) against the vector units
+             (config.solver says which of the two ran; config.sor_variant is
+             that of the sweep launches).
   cpu_baseline  the FP64 oracle on the host cores, on a bounded sample
 
 Other modes print their own JSON line: --ensemble N, --warm-start,
@@ -443,7 +445,7 @@ def bench_twinned(args, les, torch):
                                  "GB_per_s": tw_bytes / (best_tw * 1e-3) / 1e9,
                                  "hbm_frac": tw_bytes / (best_tw * 1e-3) / 8e12},
                      "red_black": {"resid": st_rb["resid"], "ms": best_rb, "us_per_iter": 1e3 * best_rb / n,
-                                   "sor_variant": int(variant)}})
+                                   "tuned_sor_variant": int(variant)}})
         log(f"{n} iterations: twinned {1e3 * best_tw / n:.1f} us/it resid {st_tw['resid']:.3e}; "
             f"red-black {1e3 * best_rb / n:.1f} us/it resid {st_rb['resid']:.3e}")
     out = {"metric": "twinned double buffering vs red-black SOR at fixed iteration counts",
@@ -633,6 +635,16 @@ def main():
     timing = g.get_timing(reset=True)
 
     value = cells * args.steps / dt_s
+    # the resident solver times every iteration of its own, checks and folds
+    # included (all of a solve, or those after the sweeps of the first 512); of
+    # the sweep launches one check interval in eight is timed
+    fused = variant >= les.NUM_SPLIT_SOR_VARIANTS
+    two = variant >= les.FIRST_TWO_ITER_SOR_VARIANT
+    iters_per_launch = 2 if two else (1 if fused else 0.5)
+    sor_ms, sor_n = timing["sor"]
+    sampled = sum(-(-(-(-int(n) // K)) // 8) for n in iters) * K / iters_per_launch
+    resident = args.sor_variant is None and sor_n not in (0, sampled)
+
     n_capped = int(st["not_converged"])
     solve = (f"red-black SOR omega={args.omega:g} to relative residual 1e-5, checked every {K} iterations "
              f"(all {args.steps} timed steps converged)"
@@ -671,14 +683,11 @@ def main():
                             "sor_iters_per_step": float(iters.mean()),
                             "sor_iters_min": int(iters.min()), "sor_iters_max": int(iters.max()),
                             "ms_per_step": dt_s * 1e3 / args.steps},
+            "solver": "resident" if resident else "sweeps",
             "sor_variant": int(variant),
             "autotune_us_per_sweep": [round(float(x), 3) for x in us],
         },
     }
-    sor_ms, sor_n = timing["sor"]
-    # the resident solver times every iteration, checks and folds included; the
-    # sweep launches are sampled (one check interval in eight)
-    resident = args.sor_variant is None and sor_n > 0 and sor_n == int(iters.sum())
     if resident:
         t_iter = sor_ms / sor_n * 1e-3
         tf = SOR_FLOPS * cells / t_iter / 1e12
@@ -690,9 +699,6 @@ def main():
                            "flops_per_cell_iteration": SOR_FLOPS, "timed_iterations": int(sor_n)}
     elif sor_n > 0:
         t_launch = sor_ms / sor_n * 1e-3
-        fused = variant >= les.NUM_SPLIT_SOR_VARIANTS
-        two = variant >= les.FIRST_TWO_ITER_SOR_VARIANT
-        iters_per_launch = 2 if two else (1 if fused else 0.5)
         # algorithmic bytes per launch = the per-cell-iteration figure of the
         # sweep's form (16 B for two half-sweeps, 12 B for a fused
         # iteration) x the cell-iterations one launch performs: 8 B/cell for

@@ -259,9 +259,9 @@ int les_pressure_solve_noalloc(les_handle* h, const float* d_rhs, float* d_p, do
 /*
  * Twinned double-buffer relaxation (section 2.6: the paper's replacement
  * for the red-black scheme on the GPU), as a measured comparison solver;
- * the time step itself uses red-black SOR.  p is held as a pair (p_0, p_1)
- * of float32 per cell, interleaved; the first half of an iteration sets
- * every cell's p_1 from p_0, the second half p_0 from p_1, each by
+ * the time step itself uses red-black SOR.  p is a pair (p_0, p_1) of
+ * float32 per cell; the first half of an iteration sets every cell's p_1
+ * from p_0, the second half p_0 from p_1, each by
  *   p_dst = p_src + omega (cn1 (sum_nb cn_nb p_src_nb - rhs) - p_src)
  * with the handle's operator.  All neighbours come from the previous half,
  * so this is a relaxed Jacobi iteration: its iterates differ from red-black
@@ -274,9 +274,10 @@ int les_pressure_solve_noalloc(les_handle* h, const float* d_rhs, float* d_p, do
  * (resid <= the handle's tol), reltmp2 = 0.  ms (optional): device time of
  * the sweeps alone (events on the stream).  Ordered on stream (NULL: the
  * handle's own), so it sees the caller's earlier writes to d_rhs and d_p on
- * that stream; returns after the stream has drained (synchronous).  Keeps a
- * workspace of (nx+2)(ny+2)(nz+2) pairs from the first call until
- * les_destroy.  LES_EINVAL for NULL pointers, iters < 0 or omega outside
+ * that stream; returns after the stream has drained (synchronous).  p_1
+ * stays in registers; two arrays of nx ny nz float32 (p_0 goes from one to
+ * the other, d_p being the first source and the last target) are kept from
+ * the first call until les_destroy.  LES_EINVAL for NULL pointers, iters < 0 or omega outside
  * (0, 1] (beyond 1 the iteration diverges on this operator);
  * LES_ENONFINITE if the residual is not finite.
  */

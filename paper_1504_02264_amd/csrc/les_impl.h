@@ -197,11 +197,12 @@ struct SolveGraph {
     hipGraphExec_t exec[3] = {nullptr, nullptr, nullptr};
     uint64_t used = 0;
 };
-// Decomposition of a grid for the resident solver (resident.hip): shape -1 if
-// the grid does not fit the chip's registers.
-// Polls of one wait of its blocks (more than a second), and of the wait for all
-// of them to come to the chip (some milliseconds).
+// Resident solver (resident.hip): polls of one wait of its blocks (more than a
+// second), and of the wait for all of them to come to the chip (some
+// milliseconds).
 constexpr int kResSpin = 1 << 21, kResGateSpin = 1 << 11;
+// Its decomposition of a grid: shape -1 if the grid does not fit the chip's
+// registers.
 struct ResPlan {
     int shape;
     int nbx, nby, nbz;   // tiles per axis

@@ -8,10 +8,11 @@
 // million cells, by the time a face value takes from one compute unit to
 // another (about 1 us per half-sweep), where the sweep launches are bound by
 // the launches (3 us each) and, from some million cells, by the 24 bytes per
-// cell and half-sweep that they move.  Per iteration against the best sweep
-// launches, MI355X: 64x64x32 with a check every 64: 2.8 us (was 7.5);
-// 150x150x90, a check every 4: 11.5 us (16.7); 300x300x90, a check every 64:
-// 11.5 us (16.5).
+// cell and half-sweep that they move.  Per iteration, checks and folds included,
+// against the best sweep launches, MI355X: 64x64x32 with a check every 64: 2.7
+// us (8.0), every 4: 3.7 (7.2); 150x150x90, every 64: 5.2 (10.6), every 4: 6.9
+// (13.2) and, in the first 512 iterations with their fold every 8, 11.0 (15.9);
+// 300x300x90, every 64: 11.4 (15.7), every 4: 13.8 (18.7).
 //
 // Same per-cell arithmetic as the sweep launches (sor_nb / sor_relax, the
 // fold's TwoSum, the float64 operator), same schedule of folds, bounds and
@@ -33,7 +34,7 @@
 // cells and are relaxed like the tile's own, with the same values, as far as
 // their surroundings reach: one column fewer per half-sweep and side.  g ghost
 // columns (2 g cells) last g iterations and are then renewed by a copy, which
-// takes a flag and two trips but only every g-th iteration (4 <= g <= 20).
+// takes a flag and two trips but only every g-th iteration (4 <= g <= 15).
 //
 // A patch's inner cells are updated first, while the last borders travel; its
 // border cells follow and are published at once.
@@ -143,12 +144,13 @@ __device__ __forceinline__ float peek(const float* p) {
 __device__ __forceinline__ void poke(float* p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-    template <int RY, int RZ, int GY>
+
+template <int RY, int RZ, int GY>
 struct Resident {
     typedef ResSmem<RY, RZ, GY> Smem;
     static_assert(RY % 2 == 0 && RZ % 2 == 0, "patch origins have even j + k, so a pair's phase is its colour");
     static constexpr int NP = RY * RZ, GZ = kResWaves / GY;
-    static constexpr bool kBig = Smem::kBig, kInner = RY > 2 && RZ > 2;   // kInner: the patch has cells inside its border
+    static constexpr bool kBig = Smem::kBig;
     static constexpr int TY = GY * RY, TZ = GZ * RZ;          // rows and planes of a tile
     static constexpr int kWords = 128 * (TY + TZ);   // face words of a block
     typedef float Patch[RY][RZ];
@@ -854,8 +856,9 @@ constexpr int kNumShapes = sizeof kShapes / sizeof kShapes[0];
 // The shape for a grid: its tiles have to fit the compute units, one block
 // each (registers: 2 waves per SIMD; LDS: all of it for the largest).  Among
 // those that fit, time goes as the pairs per thread plus the exchange between
-// tiles: per iteration 2.8 us at 4 pairs (64x64x32), 4.5 at 16 (300x300x16),
-// 5.3 at 24 (124x300x120), 9.5 to 10.5 at 48 (300x300x90).  Grids of at most
+// tiles: per iteration, with a check every 64, 2.7 us at 4 pairs (64x64x32), 4.8
+// at 16 (300x300x16), 5.8 at 24 (124x300x120), 11.4 at 48 (300x300x90; some
+// registers spilled).  Grids of at most
 // 64 half-cells per row and one tile run without the exchange.  Larger grids,
 // up to the 256 x 8 x 48 x 56 pairs that the chip holds, are refused.
 ResPlan resident_plan(const Geo& g, int cus) {
@@ -898,7 +901,8 @@ size_t resident_bytes(const ResPlan& p) {
 // most three sums and one publication per check interval
 unsigned resident_tags(int iters, int K) { return 2u * (unsigned)iters + 4u * (unsigned)(iters / K + 2) + 8u; }
 
-hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const PBufs& P, Ctl* ctl, void* mem, double omega, int K, int R, int iters, unsigned tag, unsigned launch, int spin, int gate_spin) {
+hipError_t launch_resident(const Geo& g, hipStream_t st, const ResPlan& p, const PBufs& P, Ctl* ctl, void* mem, double omega,
+                           int K, int R, int iters, unsigned tag, unsigned launch, int spin, int gate_spin) {
     if (spin < 0) return hipErrorInvalidValue;
     ResArgs a{};
     a.g = g;

@@ -51,7 +51,7 @@ __device__ __forceinline__ float tw_right(float v) {   // lane l takes lane l + 
 // 28 to 40 bytes per cell with the half-written lines: 98 us), of 150x150x90 14
 // us, of 64x64x32 5.5 us.  12 bytes per cell take 12 us at 300x300x90 at the
 // rate of a copy that stays in the Infinity Cache; the rest is the
-// chain of a march, 1.8 us per step, with 19 steps to 15 planes.  Four rows per
+// chain of a march, 1.8 us per step, with 17 steps to 15 planes.  Four rows per
 // wavefront read less twice but leave fewer wavefronts: 31, 18 and 6.7 us;
 // six: 49, 23 and 7.8.
 template <bool ODD>
